@@ -6,6 +6,9 @@
 //                   (B, Hkv, S) grid with neutral empty splits (Sec. 3.3)
 //   merge_kernel    exact segmented merge of split states (Sec. 3.3)
 //
+//   stream_kernel   the same tasks in launches with several per compute unit: a workgroup's
+//                   tasks run as one stream of pages (pairs of KV heads)
+//
 // Work mapping. One workgroup owns one task: one KV head g of one row and a token
 // range [t0, t1). Its W = 8 wavefronts (two per SIMD, one workgroup per compute unit)
 // take the range's 16-token pages round-robin, two pages in flight per wave. Two task
@@ -32,6 +35,14 @@ constexpr int D = kHeadDim;
 constexpr int P = kPageSize;
 
 typedef _Float16 h2 __attribute__((ext_vector_type(2)));
+
+// threadIdx.x, recomputed from here on: what depends on it is not kept in registers across
+// the loop around the call.
+__device__ __forceinline__ int fresh_tid() {
+  int t = threadIdx.x;
+  asm volatile("" : "+v"(t));
+  return t;
+}
 
 __device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
 
@@ -200,7 +211,7 @@ __device__ __forceinline__ void merge_group(__amdgpu_buffer_rsrc_t pr, int slot0
   float* sM = redB + kMaxMergeWaves * GH;              // [GH] max
   float* sBad = sM + GH;                               // [GH]
   float* sL = sBad + GH;                               // [GH] running L
-  const int tid = threadIdx.x;
+  const int tid = fresh_tid();
   const int lane = tid & 63;
   const int wave = tid >> 6;
   const int myh = tid % GH;  // the head of every (split, head) state this thread loads
@@ -484,44 +495,68 @@ __device__ __forceinline__ void merge_group(__amdgpu_buffer_rsrc_t pr, int slot0
 // and head, page-error flag per wave): a fixed-order combine, stored to slot `slot`.
 // NH = 2: the states of KV heads g and g + 1 (tasks `slot` and `slot` + 1), side by side
 // in LDS, each combined exactly as a one-head task's.
+// Layout of the wave states in LDS: (m, l) pairs [NH][W][G] (l = -1: the wave met an invalid
+// page), then acc [NH][W][G][kHeadPitch]. The pitch of a head's D columns puts the matrix
+// bodies' stores of several heads at once on distinct banks (at D floats the heads of one
+// store share their banks: 0.9 instead of 0.3 us per state of two KV heads).
+// `direct`: the task is its row's only split, so its state is the merged state: the output
+// goes there at once (the arithmetic of a one-split merge: weight 1, sums started at +0) and
+// no state is stored. Threads tid, tid + NT, ... take the columns.
+constexpr int kHeadPitch = D + 4;
+
+template <int G, int W, int NH = 1>
+constexpr int lds_floats() {
+  return NH * W * G * (2 + kHeadPitch);
+}
+template <int G, int W, int NH = 1>
+__device__ __forceinline__ v2f* state_ml(float* lds) { return reinterpret_cast<v2f*>(lds); }
+template <int G, int W, int NH = 1>
+__device__ __forceinline__ float* state_acc(float* lds) { return lds + 2 * NH * W * G; }
+
 template <int G, int W, bool COHERENT, int NH = 1>
-__device__ __forceinline__ void finish_task(const DecodeArgs& a, int slot, float* lds) {
-  float* lds_m = lds;                     // [NH][W][G]
-  float* lds_l = lds + NH * W * G;        // [NH][W][G]
-  float* lds_acc = lds + 2 * NH * W * G;  // [NH][W][G][D]
-  int* lds_bad = reinterpret_cast<int*>(lds + 2 * NH * W * G + NH * W * G * D);
-
-  bool any_bad = false;
-#pragma unroll
-  for (int w = 0; w < W; ++w) any_bad |= lds_bad[w] != 0;
-  if (any_bad && threadIdx.x == 0) atomicOr(a.err, (unsigned)PKV_DEVERR_PAGE_ID);
-
+__device__ __forceinline__ void finish_task(const DecodeArgs& a, int slot, float* lds, uint16_t* direct, int tid) {
   constexpr int SB = slot_floats<G>() * 4;
   constexpr int E4H = G * D / 4;  // float4 columns per head
   const __amdgpu_buffer_rsrc_t pr = slots_rsrc(a, SB);
-  for (int e4g = threadIdx.x; e4g < NH * E4H; e4g += W * 64) {
+  for (int e4g = tid; e4g < NH * E4H; e4g += W * 64) {
     const int hh = e4g / E4H;
     const int e4 = e4g - hh * E4H;
     const int h = (e4 * 4) / D;
-    const float* hm = lds_m + hh * W * G;
-    const float* hl = lds_l + hh * W * G;
-    const float* hacc = lds_acc + (size_t)hh * W * G * D;
+    const v2f* ml = state_ml<G, W, NH>(lds) + hh * W * G + h;
+    const float* hacc = state_acc<G, W, NH>(lds) + (hh * W * G + h) * kHeadPitch + (e4 * 4) % D;
     const int so = (slot + hh) * SB;
-    float M = kNegInf;
+    v2f s[W];
 #pragma unroll
-    for (int w = 0; w < W; ++w) M = fmaxf(M, hm[w * G + h]);
+    for (int w = 0; w < W; ++w) s[w] = ml[w * G];
+    float M = kNegInf;
+    bool any_bad = false;
+#pragma unroll
+    for (int w = 0; w < W; ++w) {
+      M = fmaxf(M, s[w].x);
+      any_bad |= s[w].y < 0.0f;
+    }
     const float Mref = (M == kNegInf) ? 0.0f : M;
     float L = 0.0f;
     v4f A = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
     for (int w = 0; w < W; ++w) {
-      const float cf = ex2(hm[w * G + h] - Mref);
-      const v4f x = *reinterpret_cast<const v4f*>(hacc + (size_t)w * G * D + e4 * 4);
-      L = __builtin_fmaf(cf, hl[w * G + h], L);
+      const float cf = ex2(s[w].x - Mref);
+      const v4f x = *reinterpret_cast<const v4f*>(hacc + w * G * kHeadPitch);
+      L = __builtin_fmaf(cf, s[w].y, L);
       A.x = __builtin_fmaf(cf, x.x, A.x);
       A.y = __builtin_fmaf(cf, x.y, A.y);
       A.z = __builtin_fmaf(cf, x.z, A.z);
       A.w = __builtin_fmaf(cf, x.w, A.w);
+    }
+    if (any_bad && e4 == 0) atomicOr(a.err, (unsigned)PKV_DEVERR_PAGE_ID);
+    if (direct) {
+      const bool zero = M == kNegInf || any_bad;
+      const float iL = 1.0f / L;
+      A += v4f{0.0f, 0.0f, 0.0f, 0.0f};
+      const unsigned lo = f32_to_f16_bits(zero ? 0.0f : A.x * iL) | ((unsigned)f32_to_f16_bits(zero ? 0.0f : A.y * iL) << 16);
+      const unsigned hi = f32_to_f16_bits(zero ? 0.0f : A.z * iL) | ((unsigned)f32_to_f16_bits(zero ? 0.0f : A.w * iL) << 16);
+      *reinterpret_cast<uint2*>(direct + 4 * e4g) = make_uint2(lo, hi);
+      continue;
     }
     st_state4<COHERENT>(pr, so + e4 * 16, A);
     if ((e4 * 4) % D == 0) {
@@ -609,10 +644,8 @@ struct ValuTask {
   // confirm: the wave stops, and its state is discarded).
   template <typename PlanView>
   __device__ __forceinline__ void run(const DecodeArgs& a, PlanView& plan, float* lds) {
-    float* lds_m = lds;                // [W][G]
-    float* lds_l = lds + W * G;        // [W][G]
-    float* lds_acc = lds + 2 * W * G;  // [W][G][D]
-    int* lds_bad = reinterpret_cast<int*>(lds + 2 * W * G + W * G * D);
+    v2f* lds_ml = state_ml<G, W>(lds);
+    float* lds_acc = state_acc<G, W>(lds);
     const int lane = threadIdx.x & 63;
     const int wave = uniform(threadIdx.x >> 6);
     const int r = lane >> 4;
@@ -732,18 +765,14 @@ struct ValuTask {
     if (lane < 16) {
 #pragma unroll
       for (int h = 0; h < G; ++h) {
-        float4* dst = reinterpret_cast<float4*>(lds_acc + ((size_t)wave * G + h) * D + c * 8);
+        float4* dst = reinterpret_cast<float4*>(lds_acc + (wave * G + h) * kHeadPitch + c * 8);
         dst[0] = make_float4(acc[h][0], acc[h][1], acc[h][2], acc[h][3]);
         dst[1] = make_float4(acc[h][4], acc[h][5], acc[h][6], acc[h][7]);
       }
     }
     if (lane == 0) {
 #pragma unroll
-      for (int h = 0; h < G; ++h) {
-        lds_m[wave * G + h] = m[h];
-        lds_l[wave * G + h] = l[h];
-      }
-      lds_bad[wave] = bad ? 1 : 0;
+      for (int h = 0; h < G; ++h) lds_ml[wave * G + h] = v2f{m[h], bad ? -1.0f : l[h]};
     }
     __syncthreads();
   }
@@ -799,6 +828,113 @@ template <int G>
 constexpr bool mfma_task() {
   return G > PKV_VALU_BODY_MAX_G;
 }
+
+// One page's arithmetic for one KV head, which both task bodies below share. A wave's staging
+// area holds K as [16][kKPitch] and V as [16][kVPitch] 16-byte units. Every place a lane
+// touches is one of four LDS addresses plus a constant offset; they and the two other
+// per-lane constants are formed once and kept as opaque registers (left to itself the
+// compiler keeps their parts, adds them up again on every page and spills some).
+typedef __attribute__((address_space(3))) v4u lds_v4u;
+
+__device__ __forceinline__ int opaque(int x) {
+  asm volatile("" : "+v"(x));
+  return x;
+}
+
+//
+struct PageMath {
+  int kw, kr, vw, vr;  // LDS addresses of this lane's K row piece, K operand, V row piece, V operand
+  int other;           // byte lane index of lane ^ 32
+
+  __device__ __forceinline__ void init(v4u* st) {
+    const int lane = threadIdx.x & 63, grp = lane >> 4, col = lane & 15;
+    const int base = (int)(__UINTPTR_TYPE__)(lds_v4u*)st;
+    const int vbase = base + P * kKPitch * 16;
+    kw = opaque(base + (grp * kKPitch + col) * 16);
+    kr = opaque(base + (col * kKPitch + grp) * 16);
+    vw = opaque(vbase + (grp * kVPitch + col) * 16);
+    vr = opaque(vbase + (4 * grp + (col >> 2)) * (kVPitch * 16) + (col & 3) * 8);
+    other = opaque((lane ^ 32) << 2);
+  }
+  // K token-major into LDS.
+  __device__ __forceinline__ void stage_k(const v4u (&r)[4]) const {
+    lds_v4u* at = (lds_v4u*)(unsigned)kw;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) at[4 * i * kKPitch] = r[i];
+  }
+  // V token-major; rows past t1 are zeroed (their p is 0, but 0 * NaN is not).
+  __device__ __forceinline__ void stage_v(v4u (&r)[4], int tok0, int t1) const {
+    if (tok0 + P > t1) {
+      const int tok = tok0 + ((fresh_tid() & 63) >> 4);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const unsigned keep = tok + 4 * i < t1 ? ~0u : 0u;
+        r[i] &= v4u{keep, keep, keep, keep};
+      }
+    }
+    lds_v4u* at = (lds_v4u*)(unsigned)vw;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) at[4 * i * kVPitch] = r[i];
+  }
+  // Scores of tokens 4 grp + r of head col.
+  __device__ __forceinline__ v4f scores(const v4u (&qh)[4]) const {
+    const lds_v4u* at = (const lds_v4u*)(unsigned)kr;
+    v4f sc = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+      sc = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(h8v, (v4u)at[4 * c]), __builtin_bit_cast(h8v, qh[c]),
+                                                  sc, 0, 0, 0);
+    return sc;
+  }
+  // Over the four lanes of a head: lane xor 16, then xor 32.
+  template <typename Op>
+  __device__ __forceinline__ float over_groups(float x, Op op) const {
+    x = op(x, __builtin_bit_cast(float, __builtin_amdgcn_ds_swizzle(__builtin_bit_cast(int, x), 0x401F)));
+    return op(x, __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute(other, __builtin_bit_cast(int, x))));
+  }
+  // The page's scores and staged V into (m, l, acc).
+  __device__ __forceinline__ void accumulate(v4f sc, float scale_log2, int tok0, int t1, float& m, float& l,
+                                             v4f (&acc)[D / 16]) const {
+    float x[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) x[r] = sc[r] * scale_log2;
+    if (tok0 + P > t1) {  // the row's last, partial page
+      const int tok = tok0 + 4 * ((fresh_tid() & 63) >> 4);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) x[r] = tok + r < t1 ? x[r] : kNegInf;
+    }
+    float mp = fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3]));
+    // m is the same in a head's four lanes, so the page's maximum is formed, and the state
+    // rescaled, only when a score exceeds it in some lane.
+    if (__builtin_amdgcn_ballot_w64(mp > m)) {
+      mp = over_groups(mp, [](float u, float v) { return fmaxf(u, v); });
+      if (mp > m) {
+        const float alpha = ex2(m - mp);
+        l *= alpha;
+#pragma unroll
+        for (int db = 0; db < D / 16; ++db) acc[db] *= alpha;
+        m = mp;
+      }
+    }
+    // P enters the product as fp16 hi + lo parts (p - hi is exact in fp32 and its fp16
+    // rounding leaves ~2^-22 relative), so P.V keeps the fp32 weights' accuracy
+    const float mref = (m == kNegInf) ? 0.0f : m;
+    h4v ph, pl;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const float p = ex2(x[r] - mref);
+      l += p;
+      ph[r] = (_Float16)p;
+      pl[r] = (_Float16)__builtin_fmaf((float)ph[r], -1.0f, p);
+    }
+#pragma unroll
+    for (int db = 0; db < D / 16; ++db) {
+      const h4v va_ = __builtin_bit_cast(h4v, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4v*)(unsigned)(vr + db * 32)));
+      acc[db] = __builtin_amdgcn_mfma_f32_16x16x16f16(va_, ph, acc[db], 0, 0, 0);
+      acc[db] = __builtin_amdgcn_mfma_f32_16x16x16f16(va_, pl, acc[db], 0, 0, 0);
+    }
+  }
+};
 
 // The phases and covers() are those of ValuTask. NH = 2 runs KV heads g and g + 1 of
 // the same (row, split) together: each wave reads both heads of a page (adjacent
@@ -885,10 +1021,8 @@ struct MfmaTask {
 
   template <typename PlanView>
   __device__ __forceinline__ void run(const DecodeArgs& a, PlanView& plan, float* lds) {
-    float* lds_m = lds;                     // [NH][W][G]
-    float* lds_l = lds + NH * W * G;        // [NH][W][G]
-    float* lds_acc = lds + 2 * NH * W * G;  // [NH][W][G][D]
-    int* lds_bad = reinterpret_cast<int*>(lds + 2 * NH * W * G + NH * W * G * D);
+    v2f* lds_ml = state_ml<G, W, NH>(lds);
+    float* lds_acc = state_acc<G, W, NH>(lds);
     const int lane = threadIdx.x & 63;
     const int wave = uniform(threadIdx.x >> 6);
     const int grp = lane >> 4;
@@ -903,67 +1037,18 @@ struct MfmaTask {
 #pragma unroll
       for (int db = 0; db < D / 16; ++db) acc[hh][db] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
     }
-    v4u* kst = kv_stage<W>() + wave * kStageUnits;
-    v4u* vst = kst + P * kKPitch;
-    const int tr_off = (4 * grp + (col >> 2)) * (kVPitch * 16) + (col & 3) * 8;  // + 32 db
+    PageMath pm;
+    pm.init(kv_stage<W>() + wave * kStageUnits);
 
     // one page of one head into that head's state (m, l, acc) with its query block qh
     auto consume = [&](v4u (&kr)[4], v4u (&vr)[4], int k, float& m, float& l, v4f (&acc)[D / 16],
                        const v4u (&qh)[4]) {
       const int pg = first + k * W;
       const int t1 = pg == pg_end - 1 ? plan.last_t1() : pg_end * P;  // pages before the last are whole
-      const bool tail = pg * P + P > t1;  // the row's last, partial page
-      // K token-major into LDS, read back as the A operand (token col, dims 32 c + 8 grp)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) kst[(4 * i + grp) * kKPitch + col] = kr[i];
-      v4f sc = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-      for (int c = 0; c < 4; ++c)
-        sc = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(h8v, kst[col * kKPitch + 4 * c + grp]),
-                                                    __builtin_bit_cast(h8v, qh[c]), sc, 0, 0, 0);
-      // stage V token-major; rows past t1 are zeroed (their p is 0, but 0 * NaN is not)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        v4u v = vr[i];
-        if (tail && pg * P + 4 * i + grp >= t1) v = v4u{0u, 0u, 0u, 0u};
-        vst[(4 * i + grp) * kVPitch + col] = v;
-      }
-      float x[4];
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        x[r] = sc[r] * a.scale_log2;
-        if (tail && pg * P + 4 * grp + r >= t1) x[r] = kNegInf;
-      }
-      float mp = fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3]));
-      mp = fmaxf(mp, __shfl_xor(mp, 16));
-      mp = fmaxf(mp, __shfl_xor(mp, 32));
-      if (__builtin_amdgcn_ballot_w64(mp > m)) {  // rescale only when a running max grows
-        if (mp > m) {
-          const float alpha = ex2(m - mp);
-          l *= alpha;
-#pragma unroll
-          for (int db = 0; db < D / 16; ++db) acc[db] *= alpha;
-          m = mp;
-        }
-      }
-      // P enters the product as fp16 hi + lo parts (p - hi is exact in fp32 and its fp16
-      // rounding leaves ~2^-22 relative), so P.V keeps the fp32 weights' accuracy
-      const float mref = (m == kNegInf) ? 0.0f : m;
-      h4v ph, pl;
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const float p = ex2(x[r] - mref);
-        l += p;
-        ph[r] = (_Float16)p;
-        pl[r] = (_Float16)(p - (float)ph[r]);
-      }
-#pragma unroll
-      for (int db = 0; db < D / 16; ++db) {
-        const h4v va_ = __builtin_bit_cast(h4v, __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-            (lds_s4v*)((__attribute__((address_space(3))) char*)vst + tr_off + db * 32)));
-        acc[db] = __builtin_amdgcn_mfma_f32_16x16x16f16(va_, ph, acc[db], 0, 0, 0);
-        acc[db] = __builtin_amdgcn_mfma_f32_16x16x16f16(va_, pl, acc[db], 0, 0, 0);
-      }
+      pm.stage_k(kr);
+      const v4f sc = pm.scores(qh);
+      pm.stage_v(vr, pg * P, t1);
+      pm.accumulate(sc, a.scale_log2, pg * P, t1, m, l, acc);
     };
 
     bool dropped = false;
@@ -1011,21 +1096,15 @@ struct MfmaTask {
     // wave state per head: m per head (shared by the groups), l summed over the groups, acc
 #pragma unroll
     for (int hh = 0; hh < NH; ++hh) {
-      float lw = l[hh];
-      lw += __shfl_xor(lw, 16);
-      lw += __shfl_xor(lw, 32);
+      const float lw = pm.over_groups(l[hh], [](float u, float v) { return u + v; });
       if (col < G) {
 #pragma unroll
         for (int db = 0; db < D / 16; ++db)
-          *reinterpret_cast<v4f*>(lds_acc + (((size_t)hh * W + wave) * G + col) * D + 16 * db + 4 * grp) =
+          *reinterpret_cast<v4f*>(lds_acc + ((hh * W + wave) * G + col) * kHeadPitch + 16 * db + 4 * grp) =
               acc[hh][db];
-        if (grp == 0) {
-          lds_m[(hh * W + wave) * G + col] = m[hh];
-          lds_l[(hh * W + wave) * G + col] = lw;
-        }
+        if (grp == 0) lds_ml[(hh * W + wave) * G + col] = v2f{m[hh], bad ? -1.0f : lw};
       }
     }
-    if (lane == 0) lds_bad[wave] = bad ? 1 : 0;
     __syncthreads();
   }
 };
@@ -1059,7 +1138,7 @@ __device__ __forceinline__ void run_split_task(const DecodeArgs& a, int row, int
   body.prime(a);
   KnownTask known{t1};
   body.run(a, known, lds);
-  finish_task<G, W, COHERENT>(a, slot, lds);
+  finish_task<G, W, COHERENT>(a, slot, lds, nullptr, threadIdx.x);
 }
 
 template <int G>
@@ -1074,11 +1153,6 @@ template <int G>
 __device__ __forceinline__ void zero_row(const DecodeArgs& a, int row) {
   uint32_t* o = reinterpret_cast<uint32_t*>(a.out + (size_t)row * a.Hq * D);
   for (int e = threadIdx.x; e < a.Hq * D / 2; e += blockDim.x) o[e] = 0u;
-}
-
-template <int G, int W, int NH = 1>
-constexpr int lds_floats() {
-  return NH * (2 * W * G + W * G * D) + W;
 }
 
 // ---------------------------------------------------------------------------------
@@ -1169,26 +1243,12 @@ constexpr int kCandidateRows = 16;  // batches up to this size test several quot
 // `n` is seq_lens[lane] (0 for lanes >= B), loaded by the caller.
 __device__ __forceinline__ bool wave_plan(const PlanArgs& a) { return a.B <= 64 && !a.block_table; }
 
-// seq_lens[lane] (0 for lanes >= B) through scalar loads (uniform addresses): they wait
-// on their own counter, not behind the wave's vector loads, so the planner can start as
-// soon as the lengths arrive while the task's first loads are still in flight.
-// (Loads through the constant address space with uniform addresses are scalar loads; the
-// index is clamped to the batch instead of branched on, so the loads of a group of 16 are
-// issued together.)
-typedef const __attribute__((address_space(4))) int32_t const_i32;
+// seq_lens[lane] (0 for lanes >= B). Issued ahead of the wave's other loads, so that the
+// planner waits for nothing else. (Scalar loads, 16 lengths at a time, took a round trip per
+// group: 4.6 us for 60 rows, against 1.4.)
 __device__ __forceinline__ int wave_plan_len(const PlanArgs& a) {
   const int lane = threadIdx.x & 63;
-  const int B = uniform(a.B);
-  const const_i32* lens = (const const_i32*)a.seq_lens;
-  int n = 0;
-  for (int i0 = 0; i0 < B; i0 += 16) {
-    int v[16];
-#pragma unroll
-    for (int j = 0; j < 16; ++j) v[j] = lens[min(i0 + j, B - 1)];
-#pragma unroll
-    for (int j = 0; j < 16; ++j) n = (lane == i0 + j && i0 + j < B) ? v[j] : n;
-  }
-  return n;
+  return lane < a.B ? a.seq_lens[lane] : 0;
 }
 
 __device__ __forceinline__ void plan_compute_wave(const PlanArgs& a, const PlanLds& L, bool report, int n) {
@@ -1435,13 +1495,18 @@ struct TaskRec {
   int row, g, split, t0, t1;
 };
 
-__device__ __forceinline__ TaskRec plan_task(const PlanArgs& a, const PlanLds& L, int k) {
-  const int sr = k / a.Hkv;
-  int lo = 0, hi = a.B;  // largest i with off[i] <= sr
+__device__ __forceinline__ int plan_row(const PlanLds& L, int B, int sr) {  // largest i with off[i] <= sr
+  int lo = 0, hi = B;
   while (hi - lo > 1) {
     const int mid = (lo + hi) >> 1;
     if (L.off[mid] <= sr) lo = mid; else hi = mid;
   }
+  return lo;
+}
+
+__device__ __forceinline__ TaskRec plan_task(const PlanArgs& a, const PlanLds& L, int k) {
+  const int sr = (unsigned)k / (unsigned)a.Hkv;
+  const int lo = plan_row(L, a.B, sr);
   const int T = a.tile_tokens;
   const int sp = sr - L.off[lo];
   const int n = L.len[lo];
@@ -1449,7 +1514,7 @@ __device__ __forceinline__ TaskRec plan_task(const PlanArgs& a, const PlanLds& L
   const int ns = L.off[lo + 1] - L.off[lo];
   const int b0 = split_bound(sp, tiles, ns);
   const int b1 = split_bound(sp + 1, tiles, ns);
-  return TaskRec{lo, k % a.Hkv, sp, b0 * T, min(b1 * T, n)};
+  return TaskRec{lo, k - sr * a.Hkv, sp, b0 * T, min(b1 * T, n)};
 }
 
 // The one-launch route's speculative run of the hinted task (row hr, KV head hg, first
@@ -1556,8 +1621,8 @@ __global__ __launch_bounds__(W * 64) void split_kernel(DecodeArgs a) {
   bool spec_kept = false;     // the speculative run was this workgroup's first task
   int hr = 0, hg = 0, h0 = 0, h1 = 0;  // the hinted task (h1: the plan's t1 once kept)
   // The speculative run is for one-head workgroups: with KV-head pairs its extra live
-  // state pushed the kernel past 256 registers per lane (spills in the page loop, 50%
-  // slower on the B8 traces), so a pair's hinted task is only begun and primed.
+  // state pushes the kernel past 256 registers per lane (spills in the page loop), so a
+  // pair's hinted task is only begun and primed.
   constexpr bool kSpecRun = NH == 1;
   if (PLAN) {
     if (wave_plan(a.plan)) {
@@ -1577,6 +1642,7 @@ __global__ __launch_bounds__(W * 64) void split_kernel(DecodeArgs a) {
       // scalar loads while they travel, and the planner waits only for those.
       if (threadIdx.x == 0) plan_ready = 0;
       __syncthreads();
+      const int n_raw = threadIdx.x < 64 ? wave_plan_len(a.plan) : 0;
       const bool has_hint = NH * (int)blockIdx.x < a.max_tasks;
       int hv[4] = {-1, -1, -1, -1};
       if (has_hint) {
@@ -1586,7 +1652,6 @@ __global__ __launch_bounds__(W * 64) void split_kernel(DecodeArgs a) {
         hv[2] = ld_i32<true>(tp + 3);
         hv[3] = ld_i32<true>(tp + 4);
       }
-      const int n_raw = threadIdx.x < 64 ? wave_plan_len(a.plan) : 0;
       hr = uniform(hv[0]), hg = uniform(hv[1]), h0 = uniform(hv[2]), h1 = uniform(hv[3]);
       if (has_hint && hr >= 0 && hr < a.B && hg >= 0 && hg % NH == 0 && hg + NH <= a.Hkv && h0 >= 0 && h1 > h0 &&
           h1 <= a.max_pages_per_row * P) {
@@ -1649,11 +1714,16 @@ __global__ __launch_bounds__(W * 64) void split_kernel(DecodeArgs a) {
   // arriver's merge.
   auto finish = [&](int t, int row, int g) __attribute__((always_inline)) {
     if (!FUSED) {
-      finish_task<G, W, false, NH>(a, t, lds);
+      finish_task<G, W, false, NH>(a, t, lds, nullptr, threadIdx.x);
     } else {
-      finish_task<G, W, true, NH>(a, t, lds);
       const int off = uniform(PLAN ? PL.off[row] : a.split_offsets[row]);
       int nsplit = uniform(PLAN ? PL.off[row + 1] : a.split_offsets[row + 1]) - off;
+      if (off >= 0 && nsplit == 1 && (long long)(off + 1) * a.Hkv <= a.max_tasks) {  // the row's only split
+        finish_task<G, W, true, NH>(a, t, lds, a.out + ((size_t)row * a.Hq + (size_t)g * G) * D, threadIdx.x);
+        __syncthreads();
+        return;
+      }
+      finish_task<G, W, true, NH>(a, t, lds, nullptr, threadIdx.x);
       if (off < 0 || nsplit < 1 || (long long)(off + nsplit) * a.Hkv > a.max_tasks) {
         if (threadIdx.x == 0) atomicOr(a.err, (unsigned)PKV_DEVERR_TASK);
         nsplit = 0;  // never reached by the counter: no merge from inconsistent offsets
@@ -1720,34 +1790,43 @@ __global__ __launch_bounds__(W * 64) void split_kernel(DecodeArgs a) {
   }
 }
 
-// Rectangular grid: workgroup (j, s, g) in slot order (j*S + s)*Hkv + g, where j
-// indexes the launch's rows: row_ids[j] when the launch names its rows (a length
-// bucket; Q and out are then read and written by index), else row j.
+// Rectangular grid: slot (j*S + s)*Hkv + g is split s of KV head g of launch row j, which is
+// row_ids[j] when the launch names its rows (a length bucket; Q and out are then read and
+// written by index), else row j.
+struct RectTask {
+  int row, tiles, ns, t0, t1;  // ns: the row's splits; split s of a row is empty for s >= ns
+};
+__device__ __forceinline__ RectTask rect_task(const DecodeArgs& a, int split_slot, bool report) {
+  const int s = split_slot % a.S, j = split_slot / a.S;
+  RectTask r{a.n_rows > 0 ? a.row_ids[j] : j, 0, 0, 0, 0};
+  int n = uniform(a.seq_lens[r.row]);
+  if (n < 0 || n > a.max_pages_per_row * P) {
+    if (threadIdx.x == 0 && s == 0 && report) atomicOr(a.err, (unsigned)PKV_DEVERR_SEQ_LEN);
+    n = 0;
+  }
+  const int T = a.tile_tokens;
+  r.tiles = (n + T - 1) / T;
+  r.ns = r.tiles < a.S ? r.tiles : a.S;
+  if (s < r.ns) {
+    r.t0 = uniform(split_bound(s, r.tiles, r.ns) * T);
+    r.t1 = uniform(min(split_bound(s + 1, r.tiles, r.ns) * T, n));
+  }
+  return r;
+}
+
+// One slot per workgroup, in slot order. Empty splits write the neutral state and end
+// without Q or KV traffic (Sec. 3.3).
 template <int G, int W>
 __global__ __launch_bounds__(W * 64) void rect_kernel(DecodeArgs a) {
   __shared__ float lds[lds_floats<G, W>()];
   const int slot = blockIdx.x;
   const int g = slot % a.Hkv;
-  const int s = (slot / a.Hkv) % a.S;
-  const int j = slot / (a.Hkv * a.S);
-  const int row = a.n_rows > 0 ? a.row_ids[j] : j;
-  int n = uniform(a.seq_lens[row]);
-  if (n < 0 || n > a.max_pages_per_row * P) {
-    if (threadIdx.x == 0 && s == 0 && g == 0) atomicOr(a.err, (unsigned)PKV_DEVERR_SEQ_LEN);
-    n = 0;
-  }
-  const int T = a.tile_tokens;
-  const int tiles = (n + T - 1) / T;
-  const int ns = tiles < a.S ? tiles : a.S;
-  if (s >= ns) {  // empty split: neutral state, no Q or KV traffic (Sec. 3.3)
+  const RectTask r = rect_task(a, slot / a.Hkv, g == 0);
+  if (r.t1 <= r.t0) {
     write_neutral<G>(a, slot);
     return;
   }
-  const int b0 = split_bound(s, tiles, ns);
-  const int b1 = split_bound(s + 1, tiles, ns);
-  const int t0 = b0 * T;
-  const int t1 = min(b1 * T, n);
-  run_split_task<G, W, false>(a, row, g, t0, t1, slot, lds);
+  run_split_task<G, W, false>(a, r.row, g, r.t0, r.t1, slot, lds);
 }
 
 // Segmented merge: one workgroup per (row, KV head), the same merge_group code as the
@@ -1910,18 +1989,14 @@ hipError_t launch_decode_g(const DecodeArgs& a, int mode, int grid, hipStream_t 
                            hipEvent_t stop) {
   if (mode == 2) {
     const int rows = a.n_rows > 0 ? a.n_rows : a.B;
-    hipError_t e = launch(rect_kernel<G, W>, rows * a.Hkv * a.S, W * 64, s, start, nullptr, a);
+    const int slots = rows * a.Hkv * a.S;
+    hipError_t e = launch(rect_kernel<G, W>, slots, W * 64, s, start, nullptr, a);
     if (e != hipSuccess) return e;
     return launch(merge_kernel<G, true>, rows * a.Hkv, kMergeThreads, s, nullptr, stop, a);
   }
-  if (mode == 1) {
-    static const int resident = resident_blocks((const void*)split_kernel<G, W, true, false>, W * 64);
-    return launch(split_kernel<G, W, true, false>, grid < resident ? grid : resident, W * 64, s, start, stop, a);
-  }
   if (mode == 3) {
-    // KV-head pairs when the task target gives every resident workgroup two tasks (G = 4:
-    // at G = 8 the pair merge needs two rounds of loads and the pairs ran 11% slower on
-    // the B8 traces)
+    // KV-head pairs when the task target gives every resident workgroup two tasks (at G = 8
+    // the pair merge needs two rounds of loads and the pairs ran 11% slower on the B8 traces)
     if constexpr (G == 4 && mfma_task<G>()) {  // the VALU body runs one KV head
       static const int resident2 = resident_blocks((const void*)split_kernel<G, W, true, true, 2>, W * 64);
       if (a.Hkv % 2 == 0 && a.plan.target_tasks >= 2 * resident2) {
@@ -1932,6 +2007,10 @@ hipError_t launch_decode_g(const DecodeArgs& a, int mode, int grid, hipStream_t 
     }
     static const int resident = resident_blocks((const void*)split_kernel<G, W, true, true>, W * 64);
     return launch(split_kernel<G, W, true, true>, grid < resident ? grid : resident, W * 64, s, start, stop, a);
+  }
+  if (mode == 1) {
+    static const int resident = resident_blocks((const void*)split_kernel<G, W, true, false>, W * 64);
+    return launch(split_kernel<G, W, true, false>, grid < resident ? grid : resident, W * 64, s, start, stop, a);
   }
   static const int resident = resident_blocks((const void*)split_kernel<G, W, false, false>, W * 64);
   hipError_t e = launch(split_kernel<G, W, false, false>, grid < resident ? grid : resident, W * 64, s, start,
