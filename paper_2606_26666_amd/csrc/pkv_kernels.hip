@@ -489,6 +489,74 @@ __device__ __forceinline__ void merge_group(__amdgpu_buffer_rsrc_t pr, int slot0
   }
 }
 
+// The column path for a team of GH * D / 4 threads (one KV head; thread c of the team owns
+// output elements 4c .. 4c + 3) that merges nsplit <= 64 states by itself: the runs one after
+// another, so a workgroup can merge several (row, KV head)s side by side, one per team. `ns_max`: the largest nsplit among the
+// wave's teams (G = 1 has two in a wave). wl: 128 (weight, l) pairs of LDS per wave. The
+// operations and their order are merge_group's.
+template <int G, bool COHERENT>
+__device__ __forceinline__ void merge_columns(__amdgpu_buffer_rsrc_t pr, int slot0, int stride, int nsplit, int ns_max,
+                                              int c, uint16_t* __restrict__ out_grp, v2f* wl) {
+  constexpr int SB = slot_floats<G>() * 4;
+  const int lane = fresh_tid() & 63;
+  const int hb = lane >> 5, js = lane & 31;
+  const int h = c / (D / 4);  // query head
+  const int col_at = slot0 * SB + c * 16;
+  const int ml_at = slot0 * SB + (G * D + 2 * h) * 4;
+  const int step = stride * SB;
+  const bool ok0 = js < nsplit, ok1 = js + 32 < nsplit;
+  const v2f ml0 = ld_state2<COHERENT>(pr, ok0 ? ml_at + js * step : kOutOfRange);
+  const v2f ml1 = ld_state2<COHERENT>(pr, ok1 ? ml_at + (js + 32) * step : kOutOfRange);
+  v4f v[kMergeRun];
+  auto issue = [&](int r) {
+    const int at = col_at + r * kMergeRun * step;
+#pragma unroll
+    for (int u = 0; u < kMergeRun; ++u)
+      v[u] = ld_state4<COHERENT>(pr, r * kMergeRun + u < nsplit ? at + u * step : kOutOfRange);
+  };
+  issue(0);
+  float M = fmaxf(ok0 ? ml0.x : kNegInf, ok1 ? ml1.x : kNegInf);
+  float bd = (ok0 && ml0.y < 0.0f) || (ok1 && ml1.y < 0.0f) ? 1.0f : 0.0f;
+#pragma unroll
+  for (int sh = 1; sh < 32; sh <<= 1) {  // over the half-wave
+    M = fmaxf(M, __shfl_xor(M, sh));
+    bd = fmaxf(bd, __shfl_xor(bd, sh));
+  }
+  const float Mref = (M == kNegInf) ? 0.0f : M;
+  wl[hb * 64 + js] = v2f{ok0 ? ex2(ml0.x - Mref) : 0.0f, ok0 ? ml0.y : 0.0f};
+  wl[hb * 64 + 32 + js] = v2f{ok1 ? ex2(ml1.x - Mref) : 0.0f, ok1 ? ml1.y : 0.0f};
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  v4f o = {0.0f, 0.0f, 0.0f, 0.0f};
+  float L = 0.0f;
+  const int nrun = (ns_max + kMergeRun - 1) / kMergeRun;
+#pragma clang loop unroll(disable)
+  for (int r = 0; r < nrun; ++r) {
+    v4f acc = {0.0f, 0.0f, 0.0f, 0.0f};
+    float lacc = 0.0f;
+#pragma unroll
+    for (int u = 0; u < kMergeRun; ++u) {
+      const v2f wlv = wl[hb * 64 + r * kMergeRun + u];  // zero weight and l past nsplit
+      acc.x = __builtin_fmaf(wlv.x, v[u].x, acc.x);
+      acc.y = __builtin_fmaf(wlv.x, v[u].y, acc.y);
+      acc.z = __builtin_fmaf(wlv.x, v[u].z, acc.z);
+      acc.w = __builtin_fmaf(wlv.x, v[u].w, acc.w);
+      lacc = __builtin_fmaf(wlv.x, wlv.y, lacc);
+    }
+    if (r + 1 < nrun) issue(r + 1);
+    o += acc;  // a run past the team's nsplit adds +0
+    L += lacc;
+  }
+  if (nsplit > 0) {
+    const bool zero = M == kNegInf || bd != 0.0f;
+    const float iL = 1.0f / L;
+    const unsigned lo = f32_to_f16_bits(zero ? 0.0f : o.x * iL) | ((unsigned)f32_to_f16_bits(zero ? 0.0f : o.y * iL) << 16);
+    const unsigned hi = f32_to_f16_bits(zero ? 0.0f : o.z * iL) | ((unsigned)f32_to_f16_bits(zero ? 0.0f : o.w * iL) << 16);
+    *reinterpret_cast<uint2*>(out_grp + 4 * c) = make_uint2(lo, hi);
+  }
+}
+
 // ---------------------------------------------------------------------------------
 // One task: KV head g of `row`, tokens [t0, t1), partial state into `slot`.
 // The task's partial state from the W wave states staged in LDS (m, l, acc per wave
@@ -1233,6 +1301,7 @@ struct PlanLds {
   int* wave;       // [NT / 64]
   long long* w64;  // [2 * NT / 64]
   int* wmax;       // [NT / 64]
+  int* cum = nullptr;  // [B + 1] row weights' prefix sums (plan_range_begin), when wanted
 };
 
 constexpr int kCandidateRows = 16;  // batches up to this size test several quotas per step
@@ -1329,6 +1398,11 @@ __device__ __forceinline__ void plan_compute_wave(const PlanArgs& a, const PlanL
     L.off[lane + 1] = incl;
   }
   if (lane == 0) L.off[0] = 0;
+  if (L.cum) {
+    const int wincl = wave_incl_scan(nsplit + tiles);
+    if (lane < B) L.cum[lane + 1] = wincl;
+    if (lane == 0) L.cum[0] = 0;
+  }
 }
 
 // Steps 1-3: validated lengths in L.len, split_offsets in L.off; returns the task count
@@ -1343,8 +1417,10 @@ __device__ __forceinline__ int plan_wave_tasks(const PlanArgs& a, const PlanLds&
   return (int)nt;
 }
 
+// n_first: seq_lens[threadIdx.x], when the caller has loaded it (has_first; the general path).
 template <int NT>
-__device__ __forceinline__ int plan_compute(const PlanArgs& a, const PlanLds& L, bool report) {
+__device__ __forceinline__ int plan_compute(const PlanArgs& a, const PlanLds& L, bool report, bool has_first = false,
+                                            int n_first = 0) {
   if (wave_plan(a)) {
     if (threadIdx.x < 64) plan_compute_wave(a, L, report, wave_plan_len(a));
     __syncthreads();
@@ -1361,7 +1437,7 @@ __device__ __forceinline__ int plan_compute(const PlanArgs& a, const PlanLds& L,
   const int per = (B + NT - 1) / NT;
   const int r0 = tid * per;
   for (int i = r0; i < r0 + per && i < B; ++i) {
-    int n = a.seq_lens[i];
+    int n = has_first && per == 1 ? n_first : a.seq_lens[i];
     if (n < 0 || n > cap) {
       if (report) atomicOr(a.err, (unsigned)PKV_DEVERR_SEQ_LEN);
       n = 0;
@@ -1480,6 +1556,21 @@ __device__ __forceinline__ int plan_compute(const PlanArgs& a, const PlanLds& L,
     run += row_nsplit(L.len[i]);
   }
   if (tid == NT - 1) L.off[B] = run;
+  if (L.cum) {
+    int lw = 0;
+    for (int i = r0; i < r0 + per && i < B; ++i) lw += (L.len[i] + T - 1) / T + row_nsplit(L.len[i]);
+    const int wincl = wave_incl_scan(lw);
+    __syncthreads();  // every wave has read L.wave
+    if (lane == 63) L.wave[wave] = wincl;
+    __syncthreads();
+    int at = wincl - lw;
+    for (int w = 0; w < wave; ++w) at += L.wave[w];
+    for (int i = r0; i < r0 + per && i < B; ++i) {
+      L.cum[i] = at;
+      at += (L.len[i] + T - 1) / T + row_nsplit(L.len[i]);
+    }
+    if (tid == NT - 1) L.cum[B] = at;
+  }
   __syncthreads();
   long long ntasks = (long long)L.off[B] * a.Hkv;
   if (ntasks > a.max_tasks) {  // excluded by host validation; never write past the buffer
@@ -1517,6 +1608,33 @@ __device__ __forceinline__ TaskRec plan_task(const PlanArgs& a, const PlanLds& L
   return TaskRec{lo, k - sr * a.Hkv, sp, b0 * T, min(b1 * T, n)};
 }
 
+// Units `from` .. count (per_split units a split: tasks, or pairs of them) cut into `parts`
+// contiguous ranges of about the same weight: the first unit of range w. A row's weight, its tiles plus one per split, is spread evenly over
+// its units, and a bound is a whole number of units, so that
+// neighbours agree on their common bound.
+__device__ __forceinline__ int plan_range_begin(const PlanArgs& a, const PlanLds& L, int per_split, int w, int parts, int from,
+                                                int count) {
+  if (w <= 0) return from;
+  if (w >= parts) return count;
+  auto row_of = [&](const int* v, int x) {  // largest i with v[i] <= x
+    int lo = 0, hi = a.B;
+    while (hi - lo > 1) {
+      const int mid = (lo + hi) >> 1;
+      if (v[mid] <= x) lo = mid; else hi = mid;
+    }
+    return lo;
+  };
+  const float ps = (float)per_split;
+  const int r0 = row_of(L.off, from / per_split);  // the weight in front of task `from`
+  const int n0 = L.off[r0 + 1] - L.off[r0];
+  const float w0 = (float)L.cum[r0] + (float)(L.cum[r0 + 1] - L.cum[r0]) * ((float)(from - L.off[r0] * per_split) / (ps * (float)max(n0, 1)));
+  const float x = w0 + ((float)L.cum[a.B] - w0) * ((float)w / (float)parts);
+  const int r = row_of(L.cum, (int)x);
+  const int cnt = (L.off[r + 1] - L.off[r]) * per_split, wr = max(1, L.cum[r + 1] - L.cum[r]);
+  const int k = (int)((x - (float)L.cum[r]) / (float)wr * (float)cnt + 0.5f);
+  return min(count, max(from, L.off[r] * per_split + min(max(k, 0), cnt)));
+}
+
 // The one-launch route's speculative run of the hinted task (row hr, KV head hg, first
 // token h0, h_pages pages) while wave 0 plans. Once the plan is in LDS (flag `ready`),
 // the verdict is the plan's t1 for this workgroup's first task (index `task`) if that
@@ -1549,6 +1667,12 @@ struct SpecTask {
     return verdict;
   }
 };
+
+template <int NT>
+__device__ __forceinline__ void plan_write_offsets(const PlanArgs& a, const PlanLds& L, int ntasks) {
+  for (int i = threadIdx.x; i <= a.B; i += NT) a.split_offsets[i] = L.off[i];
+  if (threadIdx.x == 0) *a.num_tasks = ntasks;
+}
 
 // The planner's outputs: split_offsets, num_tasks, the task list and zeroed completion
 // counters.
@@ -1790,6 +1914,467 @@ __global__ __launch_bounds__(W * 64) void split_kernel(DecodeArgs a) {
   }
 }
 
+// ---------------------------------------------------------------------------------
+// Streaming route: launches with more tasks than workgroups.
+//
+// A task run by itself pays a chain of dependent memory round trips around its page reads
+// (page ids, first pages, state store and its acknowledgement, completion counter, merge):
+// about 8 us in which its compute unit reads little. Here a workgroup (one per compute unit,
+// eight waves) runs its tasks as one stream of pages instead. A unit of the stream is a pair
+// of tasks, KV heads g and g + 1 of one split (adjacent 256-byte slices of every token, which
+// read faster than one head's). A wave keeps one page of each head in flight: it waits for
+// one, stages it in LDS, at once issues the loads of its next page of that head, and computes
+// from LDS. The page after a unit's last is the next unit's first, so the reads go on while a
+// unit is combined, stored, counted and merged, and what a unit leaves behind rides on the
+// waits of the ones after it: its state stores have been acknowledged when the second next
+// unit's first page is there, its completion counter is bumped in that unit's epilogue, and
+// the count is looked at two units later.
+// Every task goes through exactly the operations of the one-task kernels in their order
+// (eight waves taking its pages round-robin, the same combine and merge), so results are
+// bitwise the same.
+constexpr int kStreamRecs = 32;  // unit records a workgroup holds in LDS
+
+struct StreamRec {
+  int row, g, t0, t1, off, ns;  // row < 0: not a task of a valid plan (skipped)
+};
+
+// A wave's pages of one unit: first + k * W for k < npw.
+struct StreamSlice {
+  int row, g, first, npw, pg_end, t1;
+};
+// In scalar registers (the compiler does not see by itself that a wave's slices are uniform).
+__device__ __forceinline__ StreamSlice scalar(const StreamSlice& s) {
+  return StreamSlice{uniform(s.row), uniform(s.g), uniform(s.first), uniform(s.npw), uniform(s.pg_end), uniform(s.t1)};
+}
+
+// One head of a wave: its queries, the page in flight and the softmax state.
+struct StreamHead {
+  v4u q[4], kr[4], vr[4];
+  float m, l;
+  v4f acc[D / 16];
+
+  __device__ __forceinline__ void reset() {
+    m = kNegInf;
+    l = 0.0f;
+#pragma unroll
+    for (int db = 0; db < D / 16; ++db) acc[db] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+  }
+  // Forgets the loaded values: they are not kept in registers up to here.
+  __device__ __forceinline__ void drop() {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) asm volatile("" : "=v"(q[i]), "=v"(kr[i]), "=v"(vr[i]));
+  }
+  // The G query heads of KV head g (MFMA columns G..15 read past the descriptor: zeros).
+  template <int G>
+  __device__ __forceinline__ void load_q(const DecodeArgs& a, int row, int g) {
+    const int tid = fresh_tid();
+    const int grp = (tid & 63) >> 4, col = tid & 15;
+    const __amdgpu_buffer_rsrc_t q_rsrc = page_rsrc(a.q + ((size_t)row * a.Hq + (size_t)g * G) * D, G * D * 2);
+    const int qoff = col < G ? (col * D + 8 * grp) * 2 : kOutOfRange;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) q[c] = __builtin_amdgcn_raw_buffer_load_b128(q_rsrc, qoff, c * 64, 0);
+  }
+  // Loads of page `phys` of KV head g; unless live through an empty descriptor (zeros, no
+  // memory access), so that every path issues the same loads and the wait counts stay exact.
+  // An id outside the pool sets *bad (LDS); page 0 is read in its place.
+  __device__ __forceinline__ void issue(const DecodeArgs& a, int kv_off, int g, int phys, bool live, int* bad) {
+    const int tok_b = a.Hkv * D * 2;  // bytes between consecutive tokens
+    if (live && (unsigned)phys >= (unsigned)a.num_pages) *bad = 1;
+    phys = (unsigned)phys < (unsigned)a.num_pages ? phys : 0;
+    const int page_b = P * tok_b;
+    const size_t at = (size_t)(unsigned)phys * (unsigned)page_b;
+    const int bytes = live ? page_b : 0;
+    const __amdgpu_buffer_rsrc_t kr_rsrc = page_rsrc(reinterpret_cast<const char*>(a.k) + at, bytes);
+    const __amdgpu_buffer_rsrc_t vr_rsrc = page_rsrc(reinterpret_cast<const char*>(a.v) + at, bytes);
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      kr[i] = __builtin_amdgcn_raw_buffer_load_b128(kr_rsrc, kv_off, g * D * 2 + i * 4 * tok_b, kKvPolicy);
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      vr[i] = __builtin_amdgcn_raw_buffer_load_b128(vr_rsrc, kv_off, g * D * 2 + i * 4 * tok_b, kKvPolicy);
+  }
+  // The wave's state of a finished task into LDS.
+  template <int G>
+  __device__ __forceinline__ void dump(const PageMath& pm, float* acc_at, v2f* ml_at, bool bad) const {
+    const int lane = fresh_tid() & 63;
+    const int grp = lane >> 4, col = lane & 15;
+    const float lw = pm.over_groups(l, [](float u, float v) { return u + v; });
+    if (col < G) {
+#pragma unroll
+      for (int db = 0; db < D / 16; ++db) *reinterpret_cast<v4f*>(acc_at + col * kHeadPitch + 16 * db + 4 * grp) = acc[db];
+      if (grp == 0) ml_at[col] = v2f{m, bad ? -1.0f : lw};
+    }
+  }
+};
+
+// Workgroup barrier that orders LDS accesses and leaves global loads in flight.
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+// Waits until at most N of this wave's global loads and stores are outstanding.
+template <int N>
+__device__ __forceinline__ void vm_wait() {
+  __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
+}
+
+template <int G, int W, bool FUSED, bool PLAN>
+__global__ __launch_bounds__(W * 64) void stream_kernel(DecodeArgs a) {
+  constexpr int NH = 2;
+  __shared__ v4u stage[W * kStageUnits];             // staged pages; the plan's row weights; merge scratch
+  __shared__ float s_state[lds_floats<G, W, NH>()];  // the unit's wave states
+  __shared__ int s_bad[5 * W];                       // page-error flags: unit i's at (i % 4) * W, the hint's last
+  __shared__ int s_rec[kStreamRecs * 8];
+  __shared__ int s_list[kStreamRecs + 1];            // records whose (row, head pair) this workgroup merges; count
+  __shared__ int p_len[PLAN ? kMaxFusedPlanBatch : 1];
+  __shared__ int p_off[PLAN ? kMaxFusedPlanBatch + 1 : 1];
+  __shared__ int p_wave[W];
+  __shared__ long long p_w64[2 * W];
+  __shared__ int p_wmax[W];
+  static_assert(merge_lds_floats<G, 1, W * 64>() <= W * kStageUnits * 4, "the merge's scratch fits the staging area");
+  const PlanLds PL{p_len, p_off, p_wave, p_w64, p_wmax, reinterpret_cast<int*>(stage)};
+  const int lane = threadIdx.x & 63;
+  const int wave = uniform(threadIdx.x >> 6);
+  v4u* st = stage + wave * kStageUnits;
+  PageMath pm;
+  pm.init(st);
+  const int kv_off = opaque((lane >> 4) * (a.Hkv * D * 2) + (lane & 15) * 16);  // this lane's piece of a page's head
+
+  auto slice = [&](int row, int g, int t0, int t1) {
+    StreamSlice s;
+    s.row = row;
+    s.g = g;
+    s.t1 = t1;
+    s.pg_end = (t1 + P - 1) / P;
+    s.first = t0 / P + wave;
+    s.npw = s.first < s.pg_end ? (s.pg_end - s.first + W - 1) / W : 0;
+    return s;
+  };
+  // Ids of pages k0 .. k0 + 63 of the slice, one per lane (none is read past its pages).
+  auto load_ids = [&](const StreamSlice& s, int k0) {
+    const int tid = fresh_tid() & 63;
+    const __amdgpu_buffer_rsrc_t r = page_rsrc(a.block_table + (size_t)s.row * a.max_pages_per_row + s.first + k0 * W,
+                                               s.npw > k0 ? (s.pg_end - s.first - k0 * W) * 4 : 0);
+    return (int)__builtin_amdgcn_raw_buffer_load_b32(r, tid * (W * 4), 0, 0);
+  };
+  StreamHead h[NH];
+  StreamSlice cur, nxt{0, 0, 0, 0, 0, 0}, nn;
+  int ids = 0, ids_nxt = 0, ids_nn = 0;
+  auto start = [&](const StreamSlice& s, int id, int* bad) {  // first pages of a unit
+#pragma unroll
+    for (int hh = 0; hh < NH; ++hh) h[hh].issue(a, kv_off, s.g + hh, id, s.npw > 0, bad);
+  };
+  bool primed = false;  // h and ids_nxt hold the hinted first unit's start
+  int ht0 = 0;
+  if (threadIdx.x < 5 * W) s_bad[threadIdx.x] = 0;
+
+  // This workgroup's units: blockIdx.x, then tb + i * ts for 0 < i < n. Unit u is tasks
+  // 2u and 2u + 1.
+  int tb, ts, n;
+  const int grid = gridDim.x;
+  if (PLAN) {
+    // While the plan is formed, the waves start the unit listed at this workgroup's index by
+    // the previous launch (split_kernel's speculative start): its first pages are kept if the
+    // plan gives this workgroup the same ones. The lengths are loaded ahead of them.
+    const bool by_wave = wave_plan(a.plan);
+    int n_raw = 0;
+    if (!by_wave)
+      n_raw = (int)threadIdx.x < a.B ? a.seq_lens[threadIdx.x] : 0;
+    else if (threadIdx.x < 64)
+      n_raw = wave_plan_len(a.plan);
+    const bool has_hint = NH * (int)blockIdx.x < a.max_tasks;
+    int hv[4] = {-1, -1, -1, -1};
+    if (has_hint) {
+      const int* tp = reinterpret_cast<const int*>(a.tasks + NH * (int)blockIdx.x);
+      hv[0] = ld_i32<true>(tp + 0);
+      hv[1] = ld_i32<true>(tp + 1);
+      hv[2] = ld_i32<true>(tp + 3);
+      hv[3] = ld_i32<true>(tp + 4);
+    }
+    const int hr = uniform(hv[0]), hg = uniform(hv[1]), h1 = uniform(hv[3]);
+    ht0 = uniform(hv[2]);
+    primed = has_hint && hr >= 0 && hr < a.B && hg >= 0 && hg % NH == 0 && hg + NH <= a.Hkv && ht0 >= 0 && h1 > ht0 &&
+             h1 <= a.max_pages_per_row * P;
+    if (primed) {
+      nxt = slice(hr, hg, ht0, h1);
+      ids_nxt = load_ids(nxt, 0);
+#pragma unroll
+      for (int hh = 0; hh < NH; ++hh) h[hh].template load_q<G>(a, nxt.row, nxt.g + hh);
+    }
+    if (by_wave && threadIdx.x < 64) plan_compute_wave(a.plan, PL, blockIdx.x == 0, n_raw);
+    if (primed) start(nxt, __builtin_amdgcn_readlane(ids_nxt, 0), s_bad + 4 * W + wave);
+    int ntasks;
+    if (by_wave) {
+      lds_barrier();
+      ntasks = plan_wave_tasks(a.plan, PL, blockIdx.x == 0);
+    } else {
+      ntasks = plan_compute<W * 64>(a.plan, PL, blockIdx.x == 0, true, n_raw);
+    }
+    const int nunits = uniform(ntasks) / NH;
+    if (blockIdx.x == 0) plan_write_offsets<W * 64>(a.plan, PL, nunits * NH);
+    if (nunits <= 3 * grid) {  // few rounds: every workgroup takes the same number of units, one more or less
+      tb = blockIdx.x;
+      ts = grid;
+      n = tb < nunits ? (nunits - 1 - tb) / ts + 1 : 0;
+    } else {
+      // Contiguous ranges of about the same weight; lanes 0 and 1 find where this workgroup's
+      // and the next one's begin.
+      const int b = plan_range_begin(a.plan, PL, a.Hkv / NH, blockIdx.x + (lane & 1), grid, grid, nunits);
+      tb = __builtin_amdgcn_readlane(b, 0) - 1;
+      ts = 1;
+      n = __builtin_amdgcn_readlane(b, 1) - tb;
+    }
+  } else {
+    int ntasks = uniform(*a.num_tasks);
+    if (ntasks > a.max_tasks) ntasks = a.max_tasks;
+    const int nunits = ntasks / NH;
+    tb = blockIdx.x;
+    ts = grid;
+    n = tb < nunits ? (nunits - 1 - tb) / ts + 1 : 0;
+  }
+  // Unit i's place in the task list, in units. Ranges go through a row head pair by head pair
+  // (all splits of one, then of the next), so that the merges they end in are spread over the
+  // range; a row that the first units reach into keeps the list's order (split by split).
+  auto unit_of = [&](int i) {
+    int u = i == 0 ? (int)blockIdx.x : tb + i * ts;
+    if (PLAN && ts == 1 && i > 0) {
+      const int per = a.Hkv / NH;
+      const int row = plan_row(PL, a.B, u / per);
+      const int at = p_off[row] * per, ns = p_off[row + 1] - p_off[row];
+      if (at >= grid) u = at + (u - at) % ns * per + (u - at) / ns;
+    }
+    return u;
+  };
+
+  for (int c0 = 0; c0 < n; c0 += kStreamRecs) {  // one stream per kStreamRecs units
+    const int nc = min(kStreamRecs, n - c0);
+    if (wave == 0 && lane < nc) {  // their records
+      const int t = NH * unit_of(c0 + lane);
+      StreamRec r;
+      int split = 0;
+      if (PLAN) {
+        const TaskRec k = plan_task(a.plan, PL, t);
+        r = StreamRec{k.row, k.g, k.t0, k.t1, p_off[k.row], p_off[k.row + 1] - p_off[k.row]};
+        split = k.split;
+      } else {
+        const int* tp = reinterpret_cast<const int*>(a.tasks + t);
+        r = StreamRec{tp[0], tp[1], tp[3], tp[4], 0, 0};
+        // its partner has to be the next KV head's task of the same split, as in every plan
+        const bool pair = tp[5] == r.row && tp[6] == r.g + 1 && tp[8] == r.t0 && tp[9] == r.t1;
+        if (!pair || r.row < 0 || r.row >= a.B || r.g < 0 || r.g % NH != 0 || r.g + NH > a.Hkv || r.t0 < 0 ||
+            r.t1 <= r.t0 || r.t1 > a.max_pages_per_row * P) {  // not tasks of a valid plan: flag and skip
+          atomicOr(a.err, (unsigned)PKV_DEVERR_TASK);
+          r.row = -1;
+        } else if (FUSED) {
+          r.off = a.split_offsets[r.row];
+          r.ns = a.split_offsets[r.row + 1] - r.off;
+          if (r.off < 0 || r.ns < 1 || (long long)(r.off + r.ns) * a.Hkv > a.max_tasks) {
+            atomicOr(a.err, (unsigned)PKV_DEVERR_TASK);
+            r.ns = 0;  // never reached by the counter: no merge from inconsistent offsets
+          }
+        }
+      }
+      int* s = s_rec + lane * 8;
+      s[0] = r.row;
+      s[1] = r.g;
+      s[2] = r.t0;
+      s[3] = r.t1;
+      s[4] = r.off;
+      s[5] = r.ns;
+      s[6] = t;
+      s[7] = split;
+    }
+    if (threadIdx.x == 0) s_list[kStreamRecs] = 0;
+    lds_barrier();
+
+    auto slice_of = [&](int i) {  // an empty slice past the stream's end and for a skipped unit
+      const int* r = s_rec + min(i, nc - 1) * 8;
+      const int row = uniform(r[0]), g = uniform(r[1]), t0 = uniform(r[2]), t1 = uniform(r[3]);
+      StreamSlice s = slice(row, g, t0, t1);
+      if (i >= nc || row < 0) s = StreamSlice{0, 0, 0, 0, 0, 0};
+      return s;
+    };
+    // Thread 0's bookkeeping of stored states (-1: none): s1, s2 are the last two units'; ta
+    // and tb_ were counted in the last odd and the last even unit's epilogue, na and nb the
+    // counts read.
+    int s1 = -1, s2 = -1, ta = -1, tb_ = -1, na = 0, nb = 0;
+    auto count = [&](int i) {
+      return __hip_atomic_fetch_add(&a.counters[s_rec[i * 8] * a.Hkv + s_rec[i * 8 + 1]], 1, __ATOMIC_RELAXED,
+                                    __HIP_MEMORY_SCOPE_AGENT);
+    };
+    auto list = [&](int i, int seen) {  // the count says that it was its row's last state
+      if (i >= 0 && seen == s_rec[i * 8 + 5] - 1) {
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");  // before any wave reads the states
+        const int at = s_list[kStreamRecs];  // other waves may be reading: the entry, then the count
+        __hip_atomic_store(s_list + at, i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        __hip_atomic_store(s_list + kStreamRecs, at + 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+      }
+    };
+    // Merges of listed records. A team of kTeam threads (one column each) takes every
+    // kTeams-th head; the waves of a team need not run together. done: entries this wave has
+    // seen.
+    constexpr int kTeam = G * D / 4, kTeams = W * 64 / kTeam;
+    const __amdgpu_buffer_rsrc_t pr = slots_rsrc(a, slot_floats<G>() * 4);
+    int done = 0;
+    auto merges = [&]() __attribute__((always_inline)) {
+      const int nl = uniform(__hip_atomic_load(s_list + kStreamRecs, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
+      if (done >= NH * nl) return;
+      const int mt = fresh_tid();
+      const int team = mt / kTeam, c = mt % kTeam;
+      for (; done < NH * nl; ++done) {
+        const int* r = s_rec + s_list[done / NH] * 8;
+        const int row = uniform(r[0]), g = uniform(r[1]) + done % NH, off = uniform(r[4]), ns = uniform(r[5]);
+        const bool mine = done % kTeams == team && ns <= kColRuns * kMergeRun;
+        if (__builtin_amdgcn_ballot_w64(mine) == 0) continue;
+        merge_columns<G, true>(pr, off * a.Hkv + g, a.Hkv, mine ? ns : 0, ns, c,
+                               a.out + ((size_t)row * a.Hq + (size_t)g * G) * D, reinterpret_cast<v2f*>(st));
+        if (mine && c == 0 && g % NH == 0) a.counters[row * a.Hkv + g] = 0;
+      }
+    };
+
+    {
+      const StreamSlice s0 = slice_of(0);
+      const bool keep = c0 == 0 && primed && s0.row == nxt.row && s0.g == nxt.g && uniform(s_rec[2]) == ht0 &&
+                        s0.pg_end == nxt.pg_end;
+      nxt = s0;
+      nn = slice_of(1);
+      if (!keep) {
+        ids_nxt = load_ids(nxt, 0);
+#pragma unroll
+        for (int hh = 0; hh < NH; ++hh) h[hh].template load_q<G>(a, nxt.row, nxt.g + hh);
+      } else if (lane == 0) {
+        s_bad[wave] = s_bad[4 * W + wave];
+      }
+      ids_nn = load_ids(nn, 0);
+      if (!keep) start(nxt, __builtin_amdgcn_readlane(ids_nxt, 0), s_bad + wave);
+      vm_wait<0>();  // on every path, or the compiler would drain the stream at each unit for ids_nn
+    }
+    for (int i = 0; i < nc; ++i) {
+      // The first head's first page, and with it all that was issued before it: the unit's
+      // queries, the next one's ids, and the state stores of the unit before the last. (What
+      // may be outstanding after it: the other head's page.) A wave without pages of this
+      // unit has none in flight.
+      if (nxt.npw > 0) vm_wait<8>(); else vm_wait<0>();
+      cur = scalar(nxt);
+      ids = opaque(ids_nxt);  // copied here, behind the wait, and not at the loop's end
+      nxt = scalar(nn);
+      ids_nxt = opaque(ids_nn);
+      if (FUSED && threadIdx.x == 0) {
+        if (i & 1) list(ta, na); else list(tb_, nb);
+      }
+#pragma unroll
+      for (int hh = 0; hh < NH; ++hh) h[hh].reset();
+      int* bad = s_bad + (i % 4) * W + wave;
+      int* bad_nxt = s_bad + ((i + 1) % 4) * W + wave;
+      s_bad[((i + 2) % 4) * W + wave] = 0;  // unit i - 2 has been combined
+      int k = 0;
+#pragma clang loop unroll(disable)
+      do {  // a wave without pages of this unit goes through once, for the next one's first
+        const bool live = k < cur.npw;
+        const int pg = cur.first + k * W;
+        const int t1 = pg == cur.pg_end - 1 ? cur.t1 : cur.pg_end * P;  // pages before the last are whole
+        ++k;
+        const bool more = k < cur.npw;
+        if (more && (k & 63) == 0) {  // the next block of ids, waited for here: rare
+          ids = load_ids(cur, k);
+          vm_wait<0>();
+        }
+        if (!more) {
+          nn = slice_of(i + 2);
+          ids_nn = load_ids(nn, 0);
+        }
+        const int own = __builtin_amdgcn_readlane(ids, k & 63), other = __builtin_amdgcn_readlane(ids_nxt, 0);
+        const int phys = more ? own : other;
+#pragma unroll
+        for (int hh = 0; hh < NH; ++hh) {
+          v4f sc = {0.0f, 0.0f, 0.0f, 0.0f};
+          if (live) {
+            pm.stage_k(h[hh].kr);
+            sc = pm.scores(h[hh].q);
+            pm.stage_v(h[hh].vr, pg * P, t1);
+          }
+          if (!more) h[hh].template load_q<G>(a, nxt.row, nxt.g + hh);
+          h[hh].issue(a, kv_off, (more ? cur.g : nxt.g) + hh, phys, more || nxt.npw > 0, more ? bad : bad_nxt);
+          if (live) pm.accumulate(sc, a.scale_log2, pg * P, t1, h[hh].m, h[hh].l, h[hh].acc);
+        }
+      } while (k < cur.npw);
+      lds_barrier();  // the unit before this one has been combined
+#pragma unroll
+      for (int hh = 0; hh < NH; ++hh)
+        h[hh].template dump<G>(pm, state_acc<G, W, NH>(s_state) + (hh * W + wave) * G * kHeadPitch,
+                               state_ml<G, W, NH>(s_state) + (hh * W + wave) * G, *bad != 0);
+      lds_barrier();
+      const int* r = s_rec + i * 8;
+      const int row = uniform(r[0]), g = uniform(r[1]), ns = uniform(r[5]);
+      if (FUSED && threadIdx.x == 0) {
+        // Every wave has waited for its stores of the unit before the last: count it.
+        if (i & 1) {
+          ta = s2;
+          if (s2 >= 0) na = count(s2);
+        } else {
+          tb_ = s2;
+          if (s2 >= 0) nb = count(s2);
+        }
+        s2 = s1;
+        s1 = row >= 0 && ns != 1 ? i : -1;  // a row's only split stores no state
+      }
+      // G < 8 leaves half of the threads without a column: the halves take turns.
+      constexpr int kCols = NH * G * D / 4;
+      const int ct = fresh_tid() - (kCols <= W * 32 && (i & 1) ? W * 32 : 0);
+      if (row >= 0 && ct >= 0)
+        finish_task<G, W, FUSED, NH>(a, uniform(r[6]), s_state,
+                                     FUSED && ns == 1 ? a.out + ((size_t)row * a.Hq + (size_t)g * G) * D : nullptr, ct);
+      if (FUSED) merges();
+    }
+    if (PLAN && wave == W - 1 && lane < nc) {  // the units' tasks in the task list (off the stream's way)
+      const int* r = s_rec + lane * 8;
+      int* o = reinterpret_cast<int*>(a.plan.tasks + r[6]);
+#pragma unroll
+      for (int hh = 0; hh < NH; ++hh) {
+        o[5 * hh] = r[0];
+        o[5 * hh + 1] = r[1] + hh;
+        o[5 * hh + 2] = r[7];
+        o[5 * hh + 3] = r[2];
+        o[5 * hh + 4] = r[3];
+      }
+    }
+    if (FUSED) {  // the last counts, then the merges that are left
+      vm_wait<0>();
+      lds_barrier();
+      if (threadIdx.x == 0) {
+        list(ta, na);
+        list(tb_, nb);
+        if (s2 >= 0) list(s2, count(s2));
+        if (s1 >= 0) list(s1, count(s1));
+      }
+      lds_barrier();
+      const int nl = uniform(s_list[kStreamRecs]);
+      // Several left: side by side. One or two: by the whole workgroup, one round of loads each.
+      constexpr int kHeads = merge_lds_floats<G, NH, W * 64>() <= W * kStageUnits * 4 ? NH : 1;  // per merge_group
+      const int from = nl - uniform(done) / NH > 2 ? nl : uniform(done) / NH;
+      if (from == nl) merges();
+      for (int j = 0; j < nl; ++j) {
+        const int* r = s_rec + s_list[j] * 8;
+        const int row = uniform(r[0]), g = uniform(r[1]), off = uniform(r[4]), ns = uniform(r[5]);
+        if (j < from && ns <= kColRuns * kMergeRun) continue;
+        for (int hh = 0; hh < NH; hh += kHeads) {
+          lds_barrier();
+          merge_group<G, W * 64, true, kHeads>(pr, off * a.Hkv + g + hh, a.Hkv, ns,
+                                               a.out + ((size_t)row * a.Hq + (size_t)(g + hh) * G) * D,
+                                               reinterpret_cast<float*>(stage));
+        }
+        if (threadIdx.x == 0) a.counters[row * a.Hkv + g] = 0;
+      }
+      lds_barrier();
+    }
+    for (int hh = 0; hh < NH; ++hh) h[hh].drop();
+  }
+  if (FUSED) {  // rows without tasks: their output is zero
+    for (int i = blockIdx.x; i < a.B; i += gridDim.x) {
+      const bool empty = PLAN ? p_off[i + 1] == p_off[i] : a.split_offsets[i + 1] == a.split_offsets[i];
+      if (empty) zero_row<G>(a, i);
+    }
+  }
+}
+
 // Rectangular grid: slot (j*S + s)*Hkv + g is split s of KV head g of launch row j, which is
 // row_ids[j] when the launch names its rows (a length bucket; Q and out are then read and
 // written by index), else row j.
@@ -1984,6 +2569,31 @@ hipError_t launch(K kernel, int grid, int threads, hipStream_t s, hipEvent_t sta
   return hipGetLastError();
 }
 
+// Whether about `tasks` tasks run as a stream of KV-head pairs, `slots` (one per compute unit)
+// at a time, rather than on the one-task kernels. The stream goes through ceil(tasks / 2 slots)
+// rounds of units of two tasks each, the one-task kernels through ceil(tasks / slots) rounds
+// with a gap after each; an odd number of rounds leaves the stream half a round behind.
+// - One head per workgroup as the alternative: two rounds are one of units (the layers of 16
+//   rows 258 -> 253 us; at G = 8, whose units combine twice the states, 57 -> 59), three are
+//   two (608 tasks: 106 against 119), and from four on the gaps decide (1024 tasks 149 -> 145,
+//   62 -> 59 for short rows; G = 8: 51 -> 48 at 1024 tasks, 250 -> 155 at 8192).
+// - KV-head pairs as the alternative (`paired`: the one-launch route at G < 8): they have the
+//   same rounds and a shorter start, and win while rounds are few (1888 tasks 95.5 against
+//   96.5, 1024 tasks 276 against 278); from eight tasks per slot on the gaps decide (3200
+//   tasks 104 -> 101 and 59 -> 45 for short rows, 8192 tasks 175 -> 135).
+bool streams(int G, int Hkv, int max_tasks, int64_t tasks, int slots, bool paired) {
+  if (Hkv % 2 != 0 || max_tasks < 2) return false;
+  if (paired) return tasks >= 8 * slots;
+  const int64_t rounds = (tasks + slots - 1) / slots;
+  return rounds >= 4 || (rounds == 2 && G < 8);
+}
+
+template <int G, int W, bool FUSED, bool PLAN>
+int stream_slots() {
+  static const int r = resident_blocks((const void*)stream_kernel<G, W, FUSED, PLAN>, W * 64);
+  return r;
+}
+
 template <int G, int W>
 hipError_t launch_decode_g(const DecodeArgs& a, int mode, int grid, hipStream_t s, hipEvent_t start,
                            hipEvent_t stop) {
@@ -1995,6 +2605,13 @@ hipError_t launch_decode_g(const DecodeArgs& a, int mode, int grid, hipStream_t 
     return launch(merge_kernel<G, true>, rows * a.Hkv, kMergeThreads, s, nullptr, stop, a);
   }
   if (mode == 3) {
+    if constexpr (mfma_task<G>()) {
+    // The stream's row weights (tiles plus splits) are summed in 32 bits.
+    const int64_t weight = (int64_t)a.B * ((int64_t)a.max_pages_per_row * P / a.plan.tile_tokens + 1 + a.plan.split_max);
+    const int r = stream_slots<G, W, true, true>();
+    if (weight <= INT32_MAX && streams(G, a.Hkv, grid, a.plan.target_tasks, r, G < 8))
+      return launch(stream_kernel<G, W, true, true>, grid / 2 < r ? grid / 2 : r, W * 64, s, start, stop, a);
+    }
     // KV-head pairs when the task target gives every resident workgroup two tasks (at G = 8
     // the pair merge needs two rounds of loads and the pairs ran 11% slower on the B8 traces)
     if constexpr (G == 4 && mfma_task<G>()) {  // the VALU body runs one KV head
@@ -2008,13 +2625,30 @@ hipError_t launch_decode_g(const DecodeArgs& a, int mode, int grid, hipStream_t 
     static const int resident = resident_blocks((const void*)split_kernel<G, W, true, true>, W * 64);
     return launch(split_kernel<G, W, true, true>, grid < resident ? grid : resident, W * 64, s, start, stop, a);
   }
+  // A task list made elsewhere: its length is on the device only. The default target's
+  // four splits per row and KV head stand for it.
+  const int64_t expected = (int64_t)4 * a.B * a.Hkv;
   if (mode == 1) {
+    if constexpr (mfma_task<G>()) {
+      const int r = stream_slots<G, W, true, false>();
+      if (streams(G, a.Hkv, grid, expected, r, false))
+        return launch(stream_kernel<G, W, true, false>, grid / 2 < r ? grid / 2 : r, W * 64, s, start, stop, a);
+    }
     static const int resident = resident_blocks((const void*)split_kernel<G, W, true, false>, W * 64);
     return launch(split_kernel<G, W, true, false>, grid < resident ? grid : resident, W * 64, s, start, stop, a);
   }
-  static const int resident = resident_blocks((const void*)split_kernel<G, W, false, false>, W * 64);
-  hipError_t e = launch(split_kernel<G, W, false, false>, grid < resident ? grid : resident, W * 64, s, start,
-                        nullptr, a);
+  hipError_t e;
+  bool stream = false;
+  if constexpr (mfma_task<G>()) {
+    const int r = stream_slots<G, W, false, false>();
+    stream = streams(G, a.Hkv, grid, expected, r, false);
+    if (stream)
+      e = launch(stream_kernel<G, W, false, false>, grid / 2 < r ? grid / 2 : r, W * 64, s, start, nullptr, a);
+  }
+  if (!stream) {
+    static const int resident = resident_blocks((const void*)split_kernel<G, W, false, false>, W * 64);
+    e = launch(split_kernel<G, W, false, false>, grid < resident ? grid : resident, W * 64, s, start, nullptr, a);
+  }
   if (e != hipSuccess) return e;
   return launch(merge_kernel<G, false>, a.B * a.Hkv, kMergeThreads, s, nullptr, stop, a);
 }

@@ -1,0 +1,113 @@
+"""The stream of KV-head pairs, for launches of many tasks (one-launch, fused and two-kernel
+routes). The one-launch route streams from 2048 tasks
+on (G = 8: from 769), the routes behind pkv_plan where 4 * B * Hkv is more than 768, or more
+than 256 and up to 512 (G < 8), so a small batch with a large task target is planned and
+streamed in one launch and run task by task behind pkv_plan; both must agree bitwise."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2606_26666_amd as pkv
+from oracle import PlanParams, ref_decode, ref_plan
+from tests.gpu_cases import Case, assert_close, plan_params, read_plan, run_decode, run_plan
+
+pytestmark = pytest.mark.gpu
+
+HEADS = [(8, 8), (16, 8), (32, 8), (32, 4)]  # G = 1, 2, 4, 8
+
+
+def bufs_for(case, split_max, rect_splits=0):
+    return pkv.DecodeBuffers(case.B, case.hq, case.hkv, case.d, split_max, "cuda", rect_splits=rect_splits)
+
+
+def one_launch(case, bufs, p, lens=None, bt=None):
+    bufs.partial_region().fill_(0xFF)
+    out = torch.full((case.B, case.hq, case.d), float("nan"), dtype=torch.float16, device="cuda")
+    pkv.pkv_plan_decode(case.q_dev, case.k_dev, case.v_dev, case.bt_dev if bt is None else bt,
+                        case.lens_dev if lens is None else lens, p, bufs.tasks, bufs.split_offsets, bufs.num_tasks, 1.0,
+                        out, bufs.ws)
+    return out
+
+
+def planned(case, split_max, p, fused=True):
+    bufs = bufs_for(case, split_max)
+    run_plan(case, bufs, p)
+    out = run_decode(case, bufs, fused=fused)
+    tasks, offs = read_plan(bufs)
+    assert pkv.pkv_check_device_status(bufs.ws) == 0
+    return out, tasks, offs
+
+
+def lengths(kind, rng):
+    if kind == "edges":        # one token, one page, one tile, and one more or less of each; empty rows
+        return [1, 16, 17, 0, 33, 127, 257, 128]
+    if kind == "ragged":
+        return rng.integers(0, 3000, size=8)
+    return [40000, 13, 20001, 0, 5000]   # "long": several blocks of 64 page ids per wave
+
+
+@pytest.mark.parametrize("hq,hkv", HEADS)
+@pytest.mark.parametrize("kind,split_max,target", [("edges", 64, 4096), ("ragged", 64, 2048), ("ragged", 64, 6000),
+                                                   ("ragged", 1, 2048), ("long", 1, 2048), ("long", 200, 6400)])
+def test_stream_matches_one_task_kernels(hq, hkv, kind, split_max, target):
+    """Few and many rounds of units (strided and weighted ranges), single-page units, waves
+    without pages, rows with one split (written at once) and with more than 64; the second and third call start from the first's task list."""
+    case = Case(lengths(kind, np.random.Generator(np.random.PCG64(71))), hq=hq, hkv=hkv, seed=71)
+    assert 4 * case.B * hkv <= 256  # behind pkv_plan these run task by task
+    p = plan_params(hkv, 1, split_max, target, policy=1)
+    expect, tasks_ref, offs_ref = planned(case, split_max, p)
+    bufs = bufs_for(case, split_max)
+    for rep in range(3):
+        out = one_launch(case, bufs, p)
+        tasks, offs = read_plan(bufs)
+        assert np.array_equal(tasks, tasks_ref) and np.array_equal(offs, offs_ref), rep
+        assert torch.equal(out, expect), rep
+    assert_close(out, ref_decode(case.q, case.k, case.v, case.bt, case.lens), f"{kind} G={hq // hkv}")
+    assert pkv.pkv_check_device_status(bufs.ws) == 0
+
+
+@pytest.mark.parametrize("hq,hkv", HEADS)
+@pytest.mark.parametrize("B,target", [(64, 2100), (64, 9000), (65, 9000), (400, 40000)])
+def test_stream_of_large_batches(hq, hkv, B, target):
+    """Both planners (64 rows and more), fused and two-kernel merges over streamed states, more
+    units per workgroup than one stream holds (32; the 400 rows), and batches whose lengths change between calls on one workspace (stale hints)."""
+    rng = np.random.Generator(np.random.PCG64(72))
+    lens = rng.integers(0, 500, size=B).astype(np.int32)
+    lens[::7] = 0
+    case = Case(lens + 40, hq=hq, hkv=hkv, seed=72)
+    p = plan_params(hkv, 1, 16, target, policy=1)
+    bufs = bufs_for(case, 16)
+    for step in range(3):
+        case.lens = np.maximum(lens + 17 * step, 0).astype(np.int32)
+        case.lens[step::5] = 0
+        case.lens_dev = torch.from_numpy(case.lens).cuda()
+        out = one_launch(case, bufs, p)
+        tasks, offs = read_plan(bufs)
+        ref = ref_plan(case.lens, PlanParams(p.page_size, p.tile_tokens, hkv, 1, 16, target, 1),
+                       max_pages_per_row=case.bt.shape[1])
+        assert np.array_equal(tasks, ref[0]) and np.array_equal(offs, ref[1]), step
+        fused, _, _ = planned(case, 16, p)
+        two, _, _ = planned(case, 16, p, fused=False)
+        assert torch.equal(out, fused) and torch.equal(out, two), step
+    assert_close(out, ref_decode(case.q, case.k, case.v, case.bt, case.lens), f"B={B} G={hq // hkv}")
+    assert pkv.pkv_check_device_status(bufs.ws) == 0
+
+
+def test_stream_flags_a_bad_page_of_one_row():
+    """A page id outside the pool, in the hinted first units and elsewhere: flagged, that row's
+    output zero, every other row bitwise the clean call's."""
+    lens = np.full(20, 700, dtype=np.int32)
+    case = Case(lens, seed=73)
+    p = plan_params(8, 1, 16, 2048, policy=1)
+    bufs = bufs_for(case, 16)
+    clean = one_launch(case, bufs, p)
+    for row in (0, 11, 19):
+        bt = case.bt_dev.clone()
+        bt[row, 13] = case.num_pages + 5
+        out = one_launch(case, bufs, p, bt=bt)
+        assert pkv.pkv_check_device_status(bufs.ws) & pkv.PKV_DEVERR_PAGE_ID
+        assert torch.all(out[row] == 0)
+        keep = [i for i in range(case.B) if i != row]
+        assert torch.equal(out[keep], clean[keep]), row
+    assert torch.equal(one_launch(case, bufs, p), clean)
+    assert pkv.pkv_check_device_status(bufs.ws) == 0
