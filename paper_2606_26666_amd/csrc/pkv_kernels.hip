@@ -11,16 +11,13 @@
 //
 // Work mapping. One workgroup owns one task: one KV head g of one row and a token
 // range [t0, t1). Its W = 8 wavefronts (two per SIMD, one workgroup per compute unit)
-// take the range's 16-token pages round-robin, two pages in flight per wave. Two task
-// bodies: MfmaTask (G = 4, 8) forms Q.K^T and P.V on the matrix cores; ValuTask (G = 1,
-// 2) reads one page of one head as four 1 KiB loads
-// (lane (r, c) = (lane/16, lane%16) loads 16 bytes, dims 8c..8c+7, of token 4i+r, so
-// every load covers four whole 256-byte head rows), forms partial dot products with
-// v_dot2_f32_f16 completed by a 16-lane DPP butterfly, and runs an online softmax per
-// lane row (m, l, acc[G][8 dims]) in fp32. Each ends with an LDS combine of the W wave
-// states in a fixed order. The one-launch route can give a workgroup KV heads g and
-// g + 1 of one split instead (MfmaTask with NH = 2, one page in flight per head; G = 4),
-// which balances the per-head read rates across workgroups.
+// take the range's 16-token pages round-robin, two pages in flight per wave. MfmaTask forms
+// Q.K^T and P.V on the matrix cores, for every G = Hq / Hkv: lane (r, c) = (lane/16, lane%16)
+// loads 16 bytes, dims 8c..8c+7, of tokens 4i+r, so every load covers four whole 256-byte head
+// rows; K and V pass through LDS into the operand layouts. A task ends with an LDS combine of
+// the W wave states in a fixed order. The one-launch route can give a workgroup KV heads g and
+// g + 1 of one split instead (NH = 2, one page in flight per head; G <= 4), which balances the
+// per-head read rates across workgroups.
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 
@@ -33,8 +30,6 @@ namespace {
 
 constexpr int D = kHeadDim;
 constexpr int P = kPageSize;
-
-typedef _Float16 h2 __attribute__((ext_vector_type(2)));
 
 // threadIdx.x, recomputed from here on: what depends on it is not kept in registers across
 // the loop around the call.
@@ -49,25 +44,6 @@ __device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirs
 template <int CTRL>
 __device__ __forceinline__ float dpp(float x) {
   return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xF, 0xF, true));
-}
-
-// Sum over the 16 lanes of a DPP row; every lane of the row receives the same value.
-__device__ __forceinline__ float row_sum16(float x) {
-  x += dpp<0xB1>(x);   // quad_perm [1,0,3,2]
-  x += dpp<0x4E>(x);   // quad_perm [2,3,0,1]
-  x += dpp<0x141>(x);  // row_half_mirror
-  x += dpp<0x140>(x);  // row_mirror
-  return x;
-}
-
-__device__ __forceinline__ h2 as_h2(unsigned u) { return __builtin_bit_cast(h2, u); }
-
-__device__ __forceinline__ float dot8(const uint4& a, const uint4& b) {
-  float s = __builtin_amdgcn_fdot2(as_h2(a.x), as_h2(b.x), 0.0f, false);
-  s = __builtin_amdgcn_fdot2(as_h2(a.y), as_h2(b.y), s, false);
-  s = __builtin_amdgcn_fdot2(as_h2(a.z), as_h2(b.z), s, false);
-  s = __builtin_amdgcn_fdot2(as_h2(a.w), as_h2(b.w), s, false);
-  return s;
 }
 
 __device__ __forceinline__ float ex2(float x) { return __builtin_amdgcn_exp2f(x); }
@@ -88,19 +64,8 @@ typedef unsigned v4u __attribute__((ext_vector_type(4)));
 // 27.1 -> 25.5 us), while sc0 alone changes nothing.
 constexpr int kKvPolicy = 2;
 
-__device__ __forceinline__ uint4 kv_load16(__amdgpu_buffer_rsrc_t r, int voff, int soff) {
-  const v4u x = __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, kKvPolicy);
-  return make_uint4(x.x, x.y, x.z, x.w);
-}
-
 __device__ __forceinline__ uint16_t f32_to_f16_bits(float x) {
   return __builtin_bit_cast(uint16_t, static_cast<_Float16>(x));
-}
-
-__device__ __forceinline__ void unpack8(const uint4& u, float f[8]) {
-  h2 a = as_h2(u.x), b = as_h2(u.y), c = as_h2(u.z), d = as_h2(u.w);
-  f[0] = (float)a.x; f[1] = (float)a.y; f[2] = (float)b.x; f[3] = (float)b.y;
-  f[4] = (float)c.x; f[5] = (float)c.y; f[6] = (float)d.x; f[7] = (float)d.y;
 }
 
 constexpr float kNegInf = -__builtin_inff();
@@ -634,221 +599,11 @@ __device__ __forceinline__ void finish_task(const DecodeArgs& a, int slot, float
   }
 }
 
-// A task body runs in three phases, so that the one-launch route can issue a task's
-// first loads before its plan is known (split_kernel):
-//   begin(row, g, t0, t1)  loads Q and the wave's first 64 page ids
-//   prime()                issues the loads of the wave's first two pages (waits for the ids)
-//   run(last_t1)           the page loop, then the wave states in LDS (finish_task and
-//                          the fused route combine them into the task's partial state)
-// covers(row, g, t0, t1) tells whether a begun task read exactly what task (row, g, t0,
-// t1) reads in those phases: the same row, head and first token and the same page
-// count. t1 itself only masks tokens of the last page, which run() applies.
-template <int G, int W>
-struct ValuTask {
-  int row = 0, g = 0, t0 = 0, pg_end = 0, first = 0, npw = 0, ids = 0;  // npw = 0: no task begun
-  bool bad = false;
-  uint4 q[G];
-  uint4 ka[4], va[4], kb[4], vb[4];  // two pages in ping-pong
-
-  __device__ __forceinline__ void begin(const DecodeArgs& a, int row_, int g_, int t0_, int t1_) {
-    row = row_;
-    g = g_;
-    t0 = t0_;
-    pg_end = uniform((t1_ + P - 1) / P);
-    const int lane = threadIdx.x & 63;
-    const int wave = uniform(threadIdx.x >> 6);
-    first = uniform(t0 / P + wave);  // this wave's pages: first + k*W
-    npw = uniform(first < pg_end ? (pg_end - first + W - 1) / W : 0);
-    bad = false;
-    const uint4* qp = reinterpret_cast<const uint4*>(a.q + ((size_t)row * a.Hq + (size_t)g * G) * D) + (lane & 15);
-#pragma unroll
-    for (int h = 0; h < G; ++h) q[h] = qp[h * (D / 8)];
-    ids = lane < npw ? a.block_table[(size_t)row * a.max_pages_per_row + first + lane * W] : 0;
-  }
-
-  __device__ __forceinline__ bool covers(int row_, int g_, int t0_, int t1_) const {
-    return row_ == row && g_ == g && t0_ == t0 && (t1_ + P - 1) / P == pg_end;
-  }
-
-  // Page ids of this wave's pages sit 64 at a time in `ids`, one per lane, and are read
-  // back with v_readlane. Loads of the page in lane j of the id block into (kr, vr); a
-  // page that is not `live` is read through an empty descriptor, which returns zeros
-  // without touching memory, so the issue is branch-free.
-  __device__ __forceinline__ void issue(const DecodeArgs& a, uint4 (&kr)[4], uint4 (&vr)[4], int j, bool live) {
-    issue_page(a, kr, vr, __builtin_amdgcn_readlane(ids, j), live);
-  }
-  __device__ __forceinline__ void issue_page(const DecodeArgs& a, uint4 (&kr)[4], uint4 (&vr)[4], int phys,
-                                             bool live) {
-    const int lane = threadIdx.x & 63;
-    const size_t tok_stride = (size_t)a.Hkv * D;  // halves between consecutive tokens
-    const size_t page_stride = (size_t)P * tok_stride;
-    // byte offsets inside one page: this lane's 16 bytes of token r, and 4 tokens further
-    const int lane_off_b = (int)(((size_t)(lane >> 4) * tok_stride + (size_t)g * D + (size_t)(lane & 15) * 8) * 2);
-    const int step_b = (int)(4 * tok_stride * 2);
-    const bool ok = phys >= 0 && phys < a.num_pages;
-    bad |= live && !ok;
-    const int page_bytes = uniform(live ? (int)(page_stride * 2) : 0);
-    phys = uniform(live && ok ? phys : 0);
-    // one buffer descriptor per page (scalar registers); lanes add their 32-bit offset
-    const __amdgpu_buffer_rsrc_t kr_rsrc = page_rsrc(a.k + (size_t)phys * page_stride, page_bytes);
-    const __amdgpu_buffer_rsrc_t vr_rsrc = page_rsrc(a.v + (size_t)phys * page_stride, page_bytes);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) kr[i] = kv_load16(kr_rsrc, lane_off_b, i * step_b);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) vr[i] = kv_load16(vr_rsrc, lane_off_b, i * step_b);
-  }
-
-  // Both issues are unconditional (pages past the wave's count are not live), so every
-  // path out of prime() has waited for the id load and issued the same loads, and the
-  // page loop's wait counts stay exact.
-  __device__ __forceinline__ void prime(const DecodeArgs& a) {
-    issue(a, ka, va, 0, npw > 0);
-    issue(a, kb, vb, 1, npw > 1);
-  }
-
-  // `plan` (KnownTask or SpecTask) gives the row's token count for the task's last page
-  // (last_t1, called only by the wave that holds that page, just before consuming it)
-  // and tells whether the task was dropped (a speculative run that the plan did not
-  // confirm: the wave stops, and its state is discarded).
-  template <typename PlanView>
-  __device__ __forceinline__ void run(const DecodeArgs& a, PlanView& plan, float* lds) {
-    v2f* lds_ml = state_ml<G, W>(lds);
-    float* lds_acc = state_acc<G, W>(lds);
-    const int lane = threadIdx.x & 63;
-    const int wave = uniform(threadIdx.x >> 6);
-    const int r = lane >> 4;
-    const int c = lane & 15;
-
-    float m[G], l[G], acc[G][8];
-#pragma unroll
-    for (int h = 0; h < G; ++h) {
-      m[h] = kNegInf;
-      l[h] = 0.0f;
-#pragma unroll
-      for (int k = 0; k < 8; ++k) acc[h][k] = 0.0f;
-    }
-
-    auto consume = [&](uint4 (&kr)[4], uint4 (&vr)[4], int k) {
-      const int pg = first + k * W;
-      float x[G][4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-#pragma unroll
-        for (int h = 0; h < G; ++h) x[h][i] = row_sum16(dot8(q[h], kr[i])) * a.scale_log2;
-      }
-      const int t1 = pg == pg_end - 1 ? plan.last_t1() : pg_end * P;  // pages before the last are whole
-      if (pg * P + P > t1) {  // the row's last, partial page: mask tokens >= t1
-        const int tok = pg * P + r;  // this lane row's token in load i is tok + 4i
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const bool valid = tok + 4 * i < t1;
-#pragma unroll
-          for (int h = 0; h < G; ++h) x[h][i] = valid ? x[h][i] : kNegInf;
-          if (!valid) vr[i] = make_uint4(0, 0, 0, 0);
-        }
-      }
-      float mt[G];
-      bool grow = false;
-#pragma unroll
-      for (int h = 0; h < G; ++h) {
-        mt[h] = fmaxf(fmaxf(x[h][0], x[h][1]), fmaxf(x[h][2], x[h][3]));
-        grow |= mt[h] > m[h];
-      }
-      if (__builtin_amdgcn_ballot_w64(grow)) {  // rescale only when some running max grows
-#pragma unroll
-        for (int h = 0; h < G; ++h) {
-          if (mt[h] > m[h]) {
-            const float alpha = ex2(m[h] - mt[h]);
-            l[h] *= alpha;
-#pragma unroll
-            for (int kk = 0; kk < 8; ++kk) acc[h][kk] *= alpha;
-            m[h] = mt[h];
-          }
-        }
-      }
-      float vf[4][8];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) unpack8(vr[i], vf[i]);
-#pragma unroll
-      for (int h = 0; h < G; ++h) {
-        const float mref = (m[h] == kNegInf) ? 0.0f : m[h];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const float p = ex2(x[h][i] - mref);
-          l[h] += p;
-#pragma unroll
-          for (int kk = 0; kk < 8; ++kk) acc[h][kk] = __builtin_fmaf(p, vf[i][kk], acc[h][kk]);
-        }
-      }
-    };
-
-    // Two register buffers in ping-pong: the next page's loads are in flight while the
-    // current page is scored and accumulated. Inside the steady-state loop every load is
-    // unconditional, so each consume waits only for its own buffer's loads. begin() and
-    // prime() have fetched the first id block and issued the first two pages.
-    bool dropped = false;
-    for (int k0 = 0; k0 < npw && !dropped; k0 += 64) {
-      const int n = min(64, npw - k0);
-      if (k0 > 0) {  // begin() and prime() did this for the first id block
-        ids = (k0 + lane < npw) ? a.block_table[(size_t)row * a.max_pages_per_row + first + (k0 + lane) * W] : 0;
-        issue(a, ka, va, 0, true);
-        issue(a, kb, vb, 1, n > 1);
-      }
-      // pages j (ka) and j + 1 (kb) are in flight at the top of each iteration
-      int j = 0;
-      for (; j + 2 < n; j += 2) {
-        if ((dropped = plan.dropped())) break;
-        consume(ka, va, k0 + j);
-        issue(a, ka, va, j + 2, true);
-        consume(kb, vb, k0 + j + 1);
-        issue(a, kb, vb, (j + 3) & 63, j + 3 < n);
-      }
-      if (dropped) break;
-      consume(ka, va, k0 + j);
-      if (j + 1 < n) consume(kb, vb, k0 + j + 1);
-    }
-
-    // Combine the wave's four lane rows (butterfly over lane xor 16, then xor 32); the
-    // lanes of row 0 then hold the wave's state, which goes to LDS for a fixed-order
-    // combine of the W wave states into the task's partial state.
-#pragma unroll
-    for (int sh = 16; sh <= 32; sh <<= 1) {
-#pragma unroll
-      for (int h = 0; h < G; ++h) {
-        const float mo = __shfl_xor(m[h], sh);
-        const float lo = __shfl_xor(l[h], sh);
-        const float M = fmaxf(m[h], mo);
-        const float Mref = (M == kNegInf) ? 0.0f : M;
-        const float ca = ex2(m[h] - Mref);
-        const float cb = ex2(mo - Mref);
-        l[h] = __builtin_fmaf(cb, lo, ca * l[h]);
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-          const float ao = __shfl_xor(acc[h][k], sh);
-          acc[h][k] = __builtin_fmaf(cb, ao, ca * acc[h][k]);
-        }
-        m[h] = M;
-      }
-    }
-    if (lane < 16) {
-#pragma unroll
-      for (int h = 0; h < G; ++h) {
-        float4* dst = reinterpret_cast<float4*>(lds_acc + (wave * G + h) * kHeadPitch + c * 8);
-        dst[0] = make_float4(acc[h][0], acc[h][1], acc[h][2], acc[h][3]);
-        dst[1] = make_float4(acc[h][4], acc[h][5], acc[h][6], acc[h][7]);
-      }
-    }
-    if (lane == 0) {
-#pragma unroll
-      for (int h = 0; h < G; ++h) lds_ml[wave * G + h] = v2f{m[h], bad ? -1.0f : l[h]};
-    }
-    __syncthreads();
-  }
-};
-
 // ---------------------------------------------------------------------------------
-// The same task with both products on the matrix cores (for G = 4 and 8, where the
-// VALU form spends most of its issue slots on Q.K dot products and P.V FMAs).
+// The task body. Both products run on the matrix cores: the path is 4 flop per byte at G = 4,
+// far below their rate, but the vector form spends its issue slots on dot products and FMAs
+// (G = 4, 32 K tokens: 32.3 against 28.0 us; G = 1 and 2 stream two KV heads per workgroup this
+// way: b4 bimodal at G = 1 139 -> 129 us, b8 Zipf at G = 2 119 -> 106).
 //
 // Per 16-token page of the task's KV head, one wave computes
 //   S[16 tokens x 16] = K_page[16 x 128] . Q^T[128 x 16]       (4 x mfma 16x16x32 f16)
@@ -885,18 +640,6 @@ __device__ __forceinline__ v4u* kv_stage() {
   return stage;
 }
 
-// The matrix-core body runs G > PKV_VALU_BODY_MAX_G (default: G = 4 and 8). A library
-// built with -DPKV_VALU_BODY_MAX_G=4 (or 8) runs the VALU body up to that G instead: an
-// A/B build whose instruction and busy counters are set against the default build's to
-// back the choice of body. Results agree with the oracle either way.
-#ifndef PKV_VALU_BODY_MAX_G
-#define PKV_VALU_BODY_MAX_G 2
-#endif
-template <int G>
-constexpr bool mfma_task() {
-  return G > PKV_VALU_BODY_MAX_G;
-}
-
 // One page's arithmetic for one KV head, which both task bodies below share. A wave's staging
 // area holds K as [16][kKPitch] and V as [16][kVPitch] 16-byte units. Every place a lane
 // touches is one of four LDS addresses plus a constant offset; they and the two other
@@ -910,6 +653,13 @@ __device__ __forceinline__ int opaque(int x) {
 }
 
 //
+// The weights p = 2^(x - m) enter the product scaled by kWeightScale (a power of two, so every
+// value carries it exactly; a wave's l takes it on with its state, and the final division
+// takes it out). P is multiplied as fp16 hi + lo parts, and fp16 ends at 2^-24: scaled, a
+// weight keeps 22 bits down to 2^-28 and is lost only below 2^-39 (unscaled: 2^-14 and 2^-25,
+// where the many small weights of a long row add up to a visible part of the sum).
+constexpr float kWeightScale = 16384.0f;
+
 struct PageMath {
   int kw, kr, vw, vr;  // LDS addresses of this lane's K row piece, K operand, V row piece, V operand
   int other;           // byte lane index of lane ^ 32
@@ -992,8 +742,9 @@ struct PageMath {
     for (int r = 0; r < 4; ++r) {
       const float p = ex2(x[r] - mref);
       l += p;
-      ph[r] = (_Float16)p;
-      pl[r] = (_Float16)__builtin_fmaf((float)ph[r], -1.0f, p);
+      const float ps = p * kWeightScale;
+      ph[r] = (_Float16)ps;
+      pl[r] = (_Float16)__builtin_fmaf((float)ph[r], -1.0f, ps);
     }
 #pragma unroll
     for (int db = 0; db < D / 16; ++db) {
@@ -1004,7 +755,16 @@ struct PageMath {
   }
 };
 
-// The phases and covers() are those of ValuTask. NH = 2 runs KV heads g and g + 1 of
+// A task body runs in three phases, so that the one-launch route can issue a task's
+// first loads before its plan is known (split_kernel):
+//   begin(row, g, t0, t1)  loads Q and the wave's first 64 page ids
+//   prime()                issues the loads of the wave's first two pages (waits for the ids)
+//   run(last_t1)           the page loop, then the wave states in LDS (finish_task and
+//                          the fused route combine them into the task's partial state)
+// covers(row, g, t0, t1) tells whether a begun task read exactly what task (row, g, t0,
+// t1) reads in those phases: the same row, head and first token and the same page
+// count. t1 itself only masks tokens of the last page, which run() applies.
+// NH = 2 runs KV heads g and g + 1 of
 // the same (row, split) together: each wave reads both heads of a page (adjacent
 // 256-byte slices of every token), one page ahead per head, and keeps one softmax state
 // per head. Each head's state goes through exactly the operations the one-head body
@@ -1164,7 +924,7 @@ struct MfmaTask {
     // wave state per head: m per head (shared by the groups), l summed over the groups, acc
 #pragma unroll
     for (int hh = 0; hh < NH; ++hh) {
-      const float lw = pm.over_groups(l[hh], [](float u, float v) { return u + v; });
+      const float lw = pm.over_groups(l[hh], [](float u, float v) { return u + v; }) * kWeightScale;
       if (col < G) {
 #pragma unroll
         for (int db = 0; db < D / 16; ++db)
@@ -1184,24 +944,10 @@ struct KnownTask {
   __device__ __forceinline__ bool dropped() const { return false; }
 };
 
-// The task body each route runs: matrix-core products for G = 4 and 8, VALU otherwise
-// (one KV head per body).
-template <bool MFMA, int G, int W, int NH>
-struct BodySel {
-  static_assert(NH == 1, "the VALU body runs one KV head");
-  using type = ValuTask<G, W>;
-};
-template <int G, int W, int NH>
-struct BodySel<true, G, W, NH> {
-  using type = MfmaTask<G, W, NH>;
-};
-template <int G, int W, int NH = 1>
-using TaskBody = typename BodySel<mfma_task<G>(), G, W, NH>::type;
-
 template <int G, int W, bool COHERENT>
 __device__ __forceinline__ void run_split_task(const DecodeArgs& a, int row, int g, int t0, int t1, int slot,
                                                float* lds) {
-  TaskBody<G, W> body;
+  MfmaTask<G, W> body;
   body.begin(a, row, g, t0, t1);
   body.prime(a);
   KnownTask known{t1};
@@ -1738,7 +1484,7 @@ __global__ __launch_bounds__(W * 64) void split_kernel(DecodeArgs a) {
   // the start, so later scalar loads of them do not wait on memory (after the planner,
   // and at the end of the last task).
   asm volatile("" ::"s"(a.q), "s"(a.partials), "s"(gridDim.x));
-  TaskBody<G, W, NH> body;
+  MfmaTask<G, W, NH> body;
   bool begun = false;  // the workgroup's body holds a task begun before the plan
   int plan_ntasks = 0;
   __shared__ int plan_ready;  // wave planner: set once wave 0 has put the plan in LDS
@@ -1875,7 +1621,7 @@ __global__ __launch_bounds__(W * 64) void split_kernel(DecodeArgs a) {
   };
   // Task t (record in rec) on body `bd`, which holds a begun task when `keep`: the loads
   // it began are used if they cover task t, else the task is begun again.
-  auto task = [&](TaskBody<G, W, NH>& bd, int t, bool keep) __attribute__((always_inline)) {
+  auto task = [&](MfmaTask<G, W, NH>& bd, int t, bool keep) __attribute__((always_inline)) {
     const int row = uniform(rec[0]), g = uniform(rec[1]);
     const int t0 = uniform(rec[2]), t1 = uniform(rec[3]);
     if (row < 0 || row >= a.B || g < 0 || g % NH != 0 || g + NH > a.Hkv || t0 < 0 || t1 <= t0 ||
@@ -1903,7 +1649,7 @@ __global__ __launch_bounds__(W * 64) void split_kernel(DecodeArgs a) {
   }
   for (t += NH * gridDim.x; t + NH <= ntasks; t += NH * gridDim.x) {
     fetch(t);
-    TaskBody<G, W, NH> next;
+    MfmaTask<G, W, NH> next;
     task(next, t, false);
   }
   if (FUSED) {  // rows without tasks: their output is zero
@@ -1998,7 +1744,7 @@ struct StreamHead {
   __device__ __forceinline__ void dump(const PageMath& pm, float* acc_at, v2f* ml_at, bool bad) const {
     const int lane = fresh_tid() & 63;
     const int grp = lane >> 4, col = lane & 15;
-    const float lw = pm.over_groups(l, [](float u, float v) { return u + v; });
+    const float lw = pm.over_groups(l, [](float u, float v) { return u + v; }) * kWeightScale;
     if (col < G) {
 #pragma unroll
       for (int db = 0; db < D / 16; ++db) *reinterpret_cast<v4f*>(acc_at + col * kHeadPitch + 16 * db + 4 * grp) = acc[db];
@@ -2605,16 +2351,14 @@ hipError_t launch_decode_g(const DecodeArgs& a, int mode, int grid, hipStream_t 
     return launch(merge_kernel<G, true>, rows * a.Hkv, kMergeThreads, s, nullptr, stop, a);
   }
   if (mode == 3) {
-    if constexpr (mfma_task<G>()) {
     // The stream's row weights (tiles plus splits) are summed in 32 bits.
     const int64_t weight = (int64_t)a.B * ((int64_t)a.max_pages_per_row * P / a.plan.tile_tokens + 1 + a.plan.split_max);
     const int r = stream_slots<G, W, true, true>();
     if (weight <= INT32_MAX && streams(G, a.Hkv, grid, a.plan.target_tasks, r, G < 8))
       return launch(stream_kernel<G, W, true, true>, grid / 2 < r ? grid / 2 : r, W * 64, s, start, stop, a);
-    }
     // KV-head pairs when the task target gives every resident workgroup two tasks (at G = 8
     // the pair merge needs two rounds of loads and the pairs ran 11% slower on the B8 traces)
-    if constexpr (G == 4 && mfma_task<G>()) {  // the VALU body runs one KV head
+    if constexpr (G <= 4) {
       static const int resident2 = resident_blocks((const void*)split_kernel<G, W, true, true, 2>, W * 64);
       if (a.Hkv % 2 == 0 && a.plan.target_tasks >= 2 * resident2) {
         const int pairs = grid / 2;
@@ -2629,23 +2373,17 @@ hipError_t launch_decode_g(const DecodeArgs& a, int mode, int grid, hipStream_t 
   // four splits per row and KV head stand for it.
   const int64_t expected = (int64_t)4 * a.B * a.Hkv;
   if (mode == 1) {
-    if constexpr (mfma_task<G>()) {
-      const int r = stream_slots<G, W, true, false>();
-      if (streams(G, a.Hkv, grid, expected, r, false))
-        return launch(stream_kernel<G, W, true, false>, grid / 2 < r ? grid / 2 : r, W * 64, s, start, stop, a);
-    }
+    const int r = stream_slots<G, W, true, false>();
+    if (streams(G, a.Hkv, grid, expected, r, false))
+      return launch(stream_kernel<G, W, true, false>, grid / 2 < r ? grid / 2 : r, W * 64, s, start, stop, a);
     static const int resident = resident_blocks((const void*)split_kernel<G, W, true, false>, W * 64);
     return launch(split_kernel<G, W, true, false>, grid < resident ? grid : resident, W * 64, s, start, stop, a);
   }
   hipError_t e;
-  bool stream = false;
-  if constexpr (mfma_task<G>()) {
-    const int r = stream_slots<G, W, false, false>();
-    stream = streams(G, a.Hkv, grid, expected, r, false);
-    if (stream)
-      e = launch(stream_kernel<G, W, false, false>, grid / 2 < r ? grid / 2 : r, W * 64, s, start, nullptr, a);
-  }
-  if (!stream) {
+  const int r = stream_slots<G, W, false, false>();
+  if (streams(G, a.Hkv, grid, expected, r, false)) {
+    e = launch(stream_kernel<G, W, false, false>, grid / 2 < r ? grid / 2 : r, W * 64, s, start, nullptr, a);
+  } else {
     static const int resident = resident_blocks((const void*)split_kernel<G, W, false, false>, W * 64);
     e = launch(split_kernel<G, W, false, false>, grid < resident ? grid : resident, W * 64, s, start, nullptr, a);
   }

@@ -111,3 +111,29 @@ def test_stream_flags_a_bad_page_of_one_row():
         assert torch.equal(out[keep], clean[keep]), row
     assert torch.equal(one_launch(case, bufs, p), clean)
     assert pkv.pkv_check_device_status(bufs.ws) == 0
+
+
+@pytest.mark.parametrize("hq,hkv", HEADS)
+@pytest.mark.parametrize("target", [256, 2048])
+def test_many_small_weights_add_up(hq, hkv, target):
+    """One token holds the maximum and 40000 others have 2^-26 of its weight each, all with
+    V = 1 where the first has 0: the output is their share, 6.0e-4. fp16 weights end at 2^-24,
+    so they are only seen if the product's weights are scaled. Bound: the output's own fp16
+    rounding (2^-11) and 2^-13 (22-bit weights, 13 of whose bits lie above fp16's end)."""
+    n = 40001
+    case = Case([n], hq=hq, hkv=hkv, seed=75)
+    k = torch.zeros_like(case.k_dev)
+    v = torch.zeros_like(case.v_dev)
+    pages = case.bt_dev[0].long()
+    k[pages, :, :, 0] = -26.0 * float(np.log(2.0))
+    v[pages] = 1.0
+    k[pages[0], 0, :, 0] = 0.0
+    v[pages[0], 0] = 0.0
+    q = torch.zeros_like(case.q_dev)
+    q[:, :, 0] = 1.0
+    case.k_dev, case.v_dev, case.q_dev = k, v, q
+    p = plan_params(hkv, 1, 64, target, policy=1)
+    out = one_launch(case, bufs_for(case, 64), p).double()
+    w = float(np.exp(np.float64(k[pages[1], 0, 0, 0].item())))
+    ref = 40000 * w / (1 + 40000 * w)
+    assert float((out - ref).abs().max()) <= ref * (2.0 ** -11 + 2.0 ** -13)
