@@ -1,15 +1,16 @@
-"""The stream of KV-head pairs, for launches of many tasks (one-launch, fused and two-kernel
-routes). The one-launch route streams from 2048 tasks
+"""The kernels for launches of many tasks: the stream of KV-head pairs (one-launch, fused and
+two-kernel routes) and the dense rectangular grid. The one-launch route streams from 2048 tasks
 on (G = 8: from 769), the routes behind pkv_plan where 4 * B * Hkv is more than 768, or more
 than 256 and up to 512 (G < 8), so a small batch with a large task target is planned and
-streamed in one launch and run task by task behind pkv_plan; both must agree bitwise."""
+streamed in one launch and run task by task behind pkv_plan; both must agree bitwise.
+Rectangular grids change kernels at 1536 and 6144 slots."""
 import numpy as np
 import pytest
 import torch
 
 import paper_2606_26666_amd as pkv
 from oracle import PlanParams, ref_decode, ref_plan
-from tests.gpu_cases import Case, assert_close, plan_params, read_plan, run_decode, run_plan
+from tests.gpu_cases import Case, assert_close, plan_params, read_plan, run_decode, run_plan, run_rect
 
 pytestmark = pytest.mark.gpu
 
@@ -110,6 +111,26 @@ def test_stream_flags_a_bad_page_of_one_row():
         keep = [i for i in range(case.B) if i != row]
         assert torch.equal(out[keep], clean[keep]), row
     assert torch.equal(one_launch(case, bufs, p), clean)
+    assert pkv.pkv_check_device_status(bufs.ws) == 0
+
+
+@pytest.mark.parametrize("hq,hkv,B,S", [(8, 8, 12, 16), (32, 8, 12, 16), (32, 4, 26, 15), (16, 8, 48, 16),
+                                        (32, 8, 48, 16), (64, 8, 48, 16), (12, 3, 40, 13), (12, 3, 64, 33)])
+def test_dense_rectangular_grid(hq, hkv, B, S):
+    """1536 slots and more (one per workgroup), 6144 and more (two, for an even number of KV
+    heads), empty splits and rows: bitwise the workqueue at the same split count."""
+    rng = np.random.Generator(np.random.PCG64(74))
+    lens = rng.integers(0, 1200, size=B).astype(np.int32)
+    lens[1::6] = 0
+    lens[0] = 9000
+    case = Case(lens, hq=hq, hkv=hkv, seed=74)
+    assert B * hkv * S >= 1536
+    bufs = bufs_for(case, S, rect_splits=S)
+    run_plan(case, bufs, plan_params(hkv, S, S, 1))
+    expect = run_decode(case, bufs)
+    rect = run_rect(case, bufs, S)
+    assert torch.equal(rect, expect)
+    assert_close(rect, ref_decode(case.q, case.k, case.v, case.bt, case.lens), f"rect B={B} S={S}")
     assert pkv.pkv_check_device_status(bufs.ws) == 0
 
 
