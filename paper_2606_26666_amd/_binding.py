@@ -106,13 +106,23 @@ def _check(fn: str, st: int):
         raise PkvError(fn, st, lib().pkv_status_string(st).decode())
 
 
+# Handle of the current device's current stream, without the Stream object that
+# torch.cuda.current_stream() makes (0.2 against 1.1 us of a call).
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_current_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream(stream) -> int:
     if stream is None:
+        if _raw_stream is not None and _current_device is not None:
+            return _raw_stream(_current_device())
         stream = torch.cuda.current_stream()
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
 def _dev(t: torch.Tensor, dtype: torch.dtype, name: str) -> int:
+    if isinstance(t, torch.Tensor) and t.dtype is dtype and t.is_cuda and t.is_contiguous():
+        return t.data_ptr()
     if not isinstance(t, torch.Tensor) or not t.is_cuda:
         raise TypeError(f"{name} must be a device tensor")
     if t.dtype != dtype:

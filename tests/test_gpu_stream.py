@@ -158,3 +158,14 @@ def test_many_small_weights_add_up(hq, hkv, target):
     w = float(np.exp(np.float64(k[pages[1], 0, 0, 0].item())))
     ref = 40000 * w / (1 + 40000 * w)
     assert float((out - ref).abs().max()) <= ref * (2.0 ** -11 + 2.0 ** -13)
+
+
+@pytest.mark.parametrize("side", [False, True])
+def test_calls_go_to_the_current_stream(side):
+    """The stream a call uses when none is given is torch's current one."""
+    from paper_2606_26666_amd import _binding
+
+    s = torch.cuda.Stream() if side else torch.cuda.current_stream()
+    with torch.cuda.stream(s):
+        assert _binding._stream(None) == s.cuda_stream == torch.cuda.current_stream().cuda_stream
+    assert _binding._stream(s) == s.cuda_stream
