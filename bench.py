@@ -283,7 +283,7 @@ def page_read_us(pkv, torch, runner, flush_bufs, reps=7):
         return None
     Ev = lambda: torch.cuda.Event(enable_timing=True)  # noqa: E731
     w = runner.w
-    hpw = 2 if runner.route == "one-launch" and head_pairs(w.hq, w.hkv, w.target_tasks) else 1
+    hpw = heads_per_workgroup(runner)
     us = []
     for _ in range(reps):
         pkv.pkv_stream_read(flush_bufs[0], flush_bufs[1])
@@ -321,10 +321,20 @@ def calibrate(pkv, torch, flush_bufs, reps=10, launches=200):
 
 
 def head_pairs(hq, hkv, target):
-    """Whether the one-launch kernel runs KV-head pairs: G = 4, even Hkv and at least two
-    tasks per resident workgroup (one workgroup per compute unit)."""
+    """Whether the task target was raised for KV-head pairs: G = 4, even Hkv and at least
+    two tasks per resident workgroup (one workgroup per compute unit)."""
     from paper_2606_26666_amd import costmodel
     return costmodel.head_pairs(hq, hkv) and target >= 2 * costmodel.CUS
+
+
+def heads_per_workgroup(runner):
+    """KV heads that a workgroup of the measured decode kernel reads together: pairs on the
+    one-launch route at G <= 4 from two tasks per resident workgroup on."""
+    from paper_2606_26666_amd import costmodel
+    w = runner.w
+    pairs = head_pairs(w.hq, w.hkv, w.target_tasks) or (
+        w.hq // w.hkv <= 2 and w.hkv % 2 == 0 and w.target_tasks >= 2 * costmodel.CUS)
+    return 2 if runner.route == "one-launch" and pairs else 1
 
 
 def split_range(runner, lens):
@@ -380,8 +390,7 @@ def summarize(runner, m):
         "tasks_per_step": float(np.mean(m["ntasks"])),
         "task_target": int(w.target_tasks),
         "splits_per_row": split_range(runner, m["lens"][-1]),
-        "kv_heads_per_workgroup": 2 if runner.route == "one-launch" and head_pairs(w.hq, w.hkv, w.target_tasks)
-                                  else 1,
+        "kv_heads_per_workgroup": heads_per_workgroup(runner),
         "launches_per_step": launches_per_step(runner),
         **route_counters(runner, m),
     }

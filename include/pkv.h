@@ -187,10 +187,11 @@ int pkv_decode(const uint16_t* q, const uint16_t* k_cache, const uint16_t* v_cac
  * workgroup starts loading the task listed at its own index while the planner runs and
  * keeps those loads only if the new plan gives it the same pages. Any contents are
  * allowed (out-of-range records are ignored) and never change a result.
- * With G = 4, Hkv even and params->target_tasks at least twice the workgroups the
+ * With G <= 4, Hkv even and params->target_tasks at least twice the workgroups the
  * device holds at once (512 on MI355X), each workgroup runs two tasks together: KV heads
  * g and g + 1 of one split, whose slices of each token are adjacent (its hint is then
- * the record at twice its index). This changes only which workgroup computes what.
+ * the record at twice its index); with many tasks per workgroup (Hkv even) it runs all its
+ * pairs as one stream of pages. This changes only which workgroup computes what.
  * Outputs are bit-identical to the two-call sequence. */
 int pkv_plan_decode(const uint16_t* q, const uint16_t* k_cache, const uint16_t* v_cache,
                     int32_t num_pages, const int32_t* block_table, int32_t max_pages_per_row,

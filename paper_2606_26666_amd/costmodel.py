@@ -94,10 +94,11 @@ def slot_bytes(G: int, d: int = 128) -> int:
 
 
 def head_pairs(hq: int, hkv: int) -> bool:
-    """Whether the one-launch route runs KV heads g and g + 1 in one workgroup: G = 4
-    (the matrix-core task body; at G = 8 a pair's merge needs two rounds of loads and
+    """Whether the task target is raised so that the one-launch route runs KV heads g and
+    g + 1 in one workgroup: G = 4 (at G = 8 a pair's merge needs two rounds of loads and
     pairs measured 11% slower on the B8 traces) with an even KV-head count. The library
-    does so when the task target is at least two tasks per resident workgroup."""
+    does so, at G <= 4, when the task target is at least two tasks per resident
+    workgroup; at G = 1 and 2 the target is that high by the KV heads alone."""
     return hkv > 0 and hq % hkv == 0 and hq // hkv == 4 and hkv % 2 == 0
 
 
