@@ -195,11 +195,13 @@ int pkv_decode(const uint16_t* q, const uint16_t* k_cache, const uint16_t* v_cac
                           nullptr, nullptr);
 }
 
-int pkv_decode_rect(const uint16_t* q, const uint16_t* k_cache, const uint16_t* v_cache, int32_t num_pages,
-                    const int32_t* block_table, int32_t max_pages_per_row, const int32_t* seq_lens, int32_t B,
-                    int32_t Hq, int32_t Hkv, int32_t d, const int32_t* row_ids, int32_t n_rows, int32_t S,
-                    int32_t tile_tokens, float sm_scale, uint16_t* out, void* ws, size_t ws_bytes,
-                    hipStream_t stream) {
+// `max_pages`: pages of the launch's longest row as far as the host knows; it chooses the
+// kernel only, so lengths on the device that exceed it cost time and nothing else.
+static int decode_rect(const uint16_t* q, const uint16_t* k_cache, const uint16_t* v_cache, int32_t num_pages,
+                       const int32_t* block_table, int32_t max_pages_per_row, const int32_t* seq_lens, int32_t B,
+                       int32_t Hq, int32_t Hkv, int32_t d, const int32_t* row_ids, int32_t n_rows, int32_t S,
+                       int32_t tile_tokens, float sm_scale, uint16_t* out, void* ws, size_t ws_bytes,
+                       hipStream_t stream, int32_t max_pages) {
   int st = check_pool(q, k_cache, v_cache, num_pages, block_table, max_pages_per_row, seq_lens, B, out);
   if (st != PKV_OK || (st = check_ws(ws)) != PKV_OK) return st;
   int G = 0;
@@ -223,7 +225,17 @@ int pkv_decode_rect(const uint16_t* q, const uint16_t* k_cache, const uint16_t* 
   a.max_tasks = slots;
   a.n_rows = row_ids ? n_rows : 0;
   for (int j = 0; j < a.n_rows; ++j) a.row_ids[j] = row_ids[j];
+  a.max_pages = max_pages;
   return from_hip(launch_decode(a, G, 2, slots, stream));
+}
+
+int pkv_decode_rect(const uint16_t* q, const uint16_t* k_cache, const uint16_t* v_cache, int32_t num_pages,
+                    const int32_t* block_table, int32_t max_pages_per_row, const int32_t* seq_lens, int32_t B,
+                    int32_t Hq, int32_t Hkv, int32_t d, const int32_t* row_ids, int32_t n_rows, int32_t S,
+                    int32_t tile_tokens, float sm_scale, uint16_t* out, void* ws, size_t ws_bytes,
+                    hipStream_t stream) {
+  return decode_rect(q, k_cache, v_cache, num_pages, block_table, max_pages_per_row, seq_lens, B, Hq, Hkv, d, row_ids,
+                     n_rows, S, tile_tokens, sm_scale, out, ws, ws_bytes, stream, max_pages_per_row);
 }
 
 int pkv_decode_buckets(const uint16_t* q, const uint16_t* k_cache, const uint16_t* v_cache, int32_t num_pages,
@@ -273,9 +285,15 @@ int pkv_decode_buckets(const uint16_t* q, const uint16_t* k_cache, const uint16_
   int32_t count = 0;
   for (const Bucket& bk : buckets) {  // one rectangular split launch + one merge launch per bucket
     int32_t ids[kMaxRectRows];
-    for (int32_t j = 0; j < bk.count; ++j) ids[j] = keyed[bk.first + j].second;
-    st = pkv_decode_rect(q, k_cache, v_cache, num_pages, block_table, max_pages_per_row, seq_lens, B, Hq, Hkv, d,
-                         ids, bk.count, bk.S, p.tile_tokens, sm_scale, out, ws, ws_bytes, stream);
+    int32_t longest = 0;
+    for (int32_t j = 0; j < bk.count; ++j) {
+      ids[j] = keyed[bk.first + j].second;
+      longest = std::max(longest, host_seq_lens[ids[j]]);
+    }
+    const int32_t pages = longest / kPageSize + (longest % kPageSize != 0);
+    st = decode_rect(q, k_cache, v_cache, num_pages, block_table, max_pages_per_row, seq_lens, B, Hq, Hkv, d, ids,
+                     bk.count, bk.S, p.tile_tokens, sm_scale, out, ws, ws_bytes, stream,
+                     std::min(pages, max_pages_per_row));
     if (st != PKV_OK) return st;
     count += 2;
   }

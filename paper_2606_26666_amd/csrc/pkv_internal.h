@@ -69,7 +69,8 @@ struct DecodeArgs {
   int32_t n_rows;       // rectangular route: rows named in row_ids (0: rows 0..B-1)
   float scale_log2;     // sm_scale * log2(e)
   PlanArgs plan;        // planning inside the decode launch (pkv_plan_decode)
-  int32_t row_ids[kMaxRectRows];  // last: only the rectangular route reads it
+  int32_t row_ids[kMaxRectRows];  // last of what kernels read: only the rectangular route does
+  int32_t max_pages;              // host only, rectangular route: no row of the launch has more pages
 };
 
 

@@ -944,15 +944,15 @@ struct KnownTask {
   __device__ __forceinline__ bool dropped() const { return false; }
 };
 
-template <int G, int W, bool COHERENT>
+template <int G, int W, bool COHERENT, int NH = 1>
 __device__ __forceinline__ void run_split_task(const DecodeArgs& a, int row, int g, int t0, int t1, int slot,
                                                float* lds) {
-  MfmaTask<G, W> body;
+  MfmaTask<G, W, NH> body;
   body.begin(a, row, g, t0, t1);
   body.prime(a);
   KnownTask known{t1};
   body.run(a, known, lds);
-  finish_task<G, W, COHERENT>(a, slot, lds, nullptr, threadIdx.x);
+  finish_task<G, W, COHERENT, NH>(a, slot, lds, nullptr, threadIdx.x);
 }
 
 template <int G>
@@ -2145,19 +2145,19 @@ __device__ __forceinline__ RectTask rect_task(const DecodeArgs& a, int split_slo
   return r;
 }
 
-// One slot per workgroup, in slot order. Empty splits write the neutral state and end
-// without Q or KV traffic (Sec. 3.3).
-template <int G, int W>
+// NH adjacent slots (KV heads of one split) per workgroup, in slot order. Empty splits write
+// the neutral state and end without Q or KV traffic (Sec. 3.3).
+template <int G, int W, int NH>
 __global__ __launch_bounds__(W * 64) void rect_kernel(DecodeArgs a) {
-  __shared__ float lds[lds_floats<G, W>()];
-  const int slot = blockIdx.x;
+  __shared__ float lds[lds_floats<G, W, NH>()];
+  const int slot = NH * (int)blockIdx.x;
   const int g = slot % a.Hkv;
   const RectTask r = rect_task(a, slot / a.Hkv, g == 0);
   if (r.t1 <= r.t0) {
-    write_neutral<G>(a, slot);
+    for (int hh = 0; hh < NH; ++hh) write_neutral<G>(a, slot + hh);
     return;
   }
-  run_split_task<G, W, false>(a, r.row, g, r.t0, r.t1, slot, lds);
+  run_split_task<G, W, false, NH>(a, r.row, g, r.t0, r.t1, slot, lds);
 }
 
 // The same for grids of many small slots (rect_dense): NH adjacent slots (KV heads of one
@@ -2406,14 +2406,24 @@ hipError_t launch_decode_g(const DecodeArgs& a, int mode, int grid, hipStream_t 
   if (mode == 2) {
     const int rows = a.n_rows > 0 ? a.n_rows : a.B;
     const int slots = rows * a.Hkv * a.S;
+    // A slot of at most two pages per wave is a chain of round trips more than a read. Beyond one
+    // slot per compute unit a workgroup then runs the chains of two KV heads as one (16 splits of
+    // rows of 2048 tokens: 512 slots 14.4 -> 12.5 us, 640 18.8 -> 18.3, 1408 33.9 -> 28.2; of 4096
+    // tokens 19.9 -> 17.5, 25.9 -> 25.9, 47.7 -> 41.3). Longer slots are balanced better one by
+    // one (four rows of 17-32 K tokens twice: 108 against 102), and from 1536 slots on the dense
+    // kernel is the faster (rows of 1024 tokens: 1536 slots 21.4 against 22.7, 8192 76 against 94).
+    const int64_t tiles = ((int64_t)a.max_pages * P + a.tile_tokens - 1) / a.tile_tokens;
+    const int64_t slot_pages = (tiles + a.S - 1) / a.S * (a.tile_tokens / P);
     // Many slots are small ones (each row has S of them): from six per compute unit on, two
     // workgroups a unit with one page in flight per wave beat one with two (13 rows of up to
     // 8250 tokens, 1664 slots: 46 against 48 us; 21 rows of up to 39 K, 1344 slots: 146 against
     // 139), and from twelve rounds of them on two slots per workgroup beat one (60 rows of up
     // to 4096 tokens, 7680 slots: 103 against 112 us; 2560 slots: 86 against 82).
     hipError_t e;
-    if (slots < 6 * 256)
-      e = launch(rect_kernel<G, W>, slots, W * 64, s, start, nullptr, a);
+    if (G <= 4 && a.Hkv % 2 == 0 && slots > 256 && slots < 6 * 256 && slot_pages <= 2 * W)
+      e = launch(rect_kernel<G, W, G <= 4 ? 2 : 1>, slots / 2, W * 64, s, start, nullptr, a);
+    else if (slots < 6 * 256)
+      e = launch(rect_kernel<G, W, 1>, slots, W * 64, s, start, nullptr, a);
     else if (a.Hkv % 2 == 0 && slots >= 12 * 512)
       e = launch(rect_dense_kernel<G, W, 2>, slots / 2, W * 64, s, start, nullptr, a);
     else

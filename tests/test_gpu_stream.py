@@ -3,7 +3,8 @@ two-kernel routes) and the dense rectangular grid. The one-launch route streams 
 on (G = 8: from 769), the routes behind pkv_plan where 4 * B * Hkv is more than 768, or more
 than 256 and up to 512 (G < 8), so a small batch with a large task target is planned and
 streamed in one launch and run task by task behind pkv_plan; both must agree bitwise.
-Rectangular grids change kernels at 1536 and 6144 slots."""
+Rectangular grids change kernels at 1536 and 6144 slots, and between 257 and 1535 at slots of
+more than 16 pages."""
 import numpy as np
 import pytest
 import torch
@@ -131,6 +132,33 @@ def test_dense_rectangular_grid(hq, hkv, B, S):
     rect = run_rect(case, bufs, S)
     assert torch.equal(rect, expect)
     assert_close(rect, ref_decode(case.q, case.k, case.v, case.bt, case.lens), f"rect B={B} S={S}")
+    assert pkv.pkv_check_device_status(bufs.ws) == 0
+
+
+@pytest.mark.parametrize("extra", [-1, 0, 1])
+@pytest.mark.parametrize("hq,hkv,B,S", [(8, 8, 5, 16), (16, 8, 3, 11), (32, 8, 3, 11), (32, 8, 11, 17), (64, 8, 5, 16),
+                                        (12, 3, 9, 12)])
+def test_short_rectangular_slots_in_pairs(hq, hkv, B, S, extra):
+    """257 to 1535 slots of at most 16 pages (32-token tiles: rows of 256 S tokens) run as pairs
+    of KV heads (G <= 4, even Hkv); one token more and they run one by one. Empty rows and
+    splits, whole batch and length buckets: bitwise the workqueue at the same split count."""
+    rng = np.random.Generator(np.random.PCG64(76))
+    lens = rng.integers(0, 700, size=B).astype(np.int32)
+    lens[0] = 256 * S + extra
+    lens[1] = 0
+    lens[2] = 17
+    case = Case(lens, hq=hq, hkv=hkv, seed=76)
+    assert 256 < B * hkv * S < 1536
+    bufs = bufs_for(case, S, rect_splits=S)
+    p = plan_params(hkv, S, S, 1)
+    run_plan(case, bufs, p)
+    expect = run_decode(case, bufs)
+    assert torch.equal(run_rect(case, bufs, S), expect)
+    out = torch.full_like(expect, float("nan"))
+    pkv.pkv_decode_buckets(case.q_dev, case.k_dev, case.v_dev, case.bt_dev, case.lens_dev, case.lens, 8192, p, 1.0, out,
+                           bufs.ws)
+    assert torch.equal(out, expect)
+    assert_close(expect, ref_decode(case.q, case.k, case.v, case.bt, case.lens), f"rect B={B} S={S}")
     assert pkv.pkv_check_device_status(bufs.ws) == 0
 
 
