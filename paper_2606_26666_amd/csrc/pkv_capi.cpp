@@ -285,11 +285,13 @@ int pkv_decode_buckets(const uint16_t* q, const uint16_t* k_cache, const uint16_
   int32_t count = 0;
   for (const Bucket& bk : buckets) {  // one rectangular split launch + one merge launch per bucket
     int32_t ids[kMaxRectRows];
-    int32_t longest = 0;
-    for (int32_t j = 0; j < bk.count; ++j) {
-      ids[j] = keyed[bk.first + j].second;
-      longest = std::max(longest, host_seq_lens[ids[j]]);
-    }
+    for (int32_t j = 0; j < bk.count; ++j) ids[j] = keyed[bk.first + j].second;
+    // Longest rows first: every row has the same number of slots, so the long ones are the long
+    // slots, and the short ones even out what the compute units have left (16 rows of up to 24 K
+    // tokens 139 -> 131 us, 64 of up to 4096 115 -> 111, at G = 8 eight rows 51.5 -> 47.8; over 50
+    // batches between 1.6% slower and 7.9% faster, 1.5% faster on average).
+    std::stable_sort(ids, ids + bk.count, [&](int32_t x, int32_t y) { return host_seq_lens[x] > host_seq_lens[y]; });
+    const int32_t longest = host_seq_lens[ids[0]];
     const int32_t pages = longest / kPageSize + (longest % kPageSize != 0);
     st = decode_rect(q, k_cache, v_cache, num_pages, block_table, max_pages_per_row, seq_lens, B, Hq, Hkv, d, ids,
                      bk.count, bk.S, p.tile_tokens, sm_scale, out, ws, ws_bytes, stream,
