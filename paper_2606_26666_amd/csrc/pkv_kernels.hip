@@ -2110,6 +2110,8 @@ __global__ __launch_bounds__(W * 64) void stream_kernel(DecodeArgs a) {
         if (threadIdx.x == 0) a.counters[row * a.Hkv + g] = 0;
       }
       lds_barrier();
+    } else {
+      lds_barrier();  // every wave has read its last unit's record: the next stream's may be written
     }
     for (int hh = 0; hh < NH; ++hh) h[hh].drop();
   }
