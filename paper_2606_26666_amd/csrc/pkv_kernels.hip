@@ -1810,7 +1810,7 @@ __global__ __launch_bounds__(W * 64) void stream_kernel(DecodeArgs a) {
   };
   bool primed = false;  // h and ids_nxt hold the hinted first unit's start
   int ht0 = 0;
-  if (threadIdx.x < 5 * W) s_bad[threadIdx.x] = 0;
+  if (lane < 5) s_bad[lane * W + wave] = 0;  // each wave its own: it sets them before any barrier
 
   // This workgroup's units: blockIdx.x, then tb + i * ts for 0 < i < n. Unit u is tasks
   // 2u and 2u + 1.

@@ -50,3 +50,24 @@ def test_more_units_than_one_stream_holds(program, route, hq, hkv, order):
     assert any(k.startswith("stream_kernel") for k in kernels(launched)), launched
     assert a.status == 0 and a.error_bits == 0 and a.counters_left == 0 and a.num_tasks == 70 * hkv
     close(a.out, reference(c), f"{route} G={hq // hkv}")
+
+
+@pytest.mark.parametrize("order", SCHEDULES)
+@pytest.mark.parametrize("hq,hkv", HEADS)
+@pytest.mark.parametrize("page", [0, 3, 7])
+def test_bad_page_of_a_hinted_unit_is_kept(program, hq, hkv, page, order):
+    """The second call starts from the first one's list, so each wave reads its first page of unit 0
+    while the plan is formed: a page id outside the pool is flagged then, and the row is zero.
+    With wave 0 last, the waves that set the flag are past it when wave 0 begins."""
+    lens = [128] * 6 + [40]
+    c = Call([lens, lens], hq=hq, hkv=hkv, seed=4)
+    c.bt[0, page] = c.num_pages + 3
+    answers, launched = c.run(program, "plan_decode", params(hkv, split_max=1), order=order, compute_units=2)
+    assert kernels(launched)[0].startswith("stream_kernel"), launched
+    bt = c.bt.copy()
+    bt[0, page] = 0
+    ref = ref_decode(c.q, c.k, c.v, bt, c.lens[0])
+    for n, a in enumerate(answers):
+        assert a.error_bits == PAGE_ID and a.counters_left == 0, (n, a.error_bits)
+        assert np.all(a.out[0] == 0), n
+        close(a.out[1:], ref[1:], n)
