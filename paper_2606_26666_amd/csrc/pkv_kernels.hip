@@ -1961,7 +1961,7 @@ __global__ __launch_bounds__(W * 64) void stream_kernel(DecodeArgs a) {
     const __amdgpu_buffer_rsrc_t pr = slots_rsrc(a, slot_floats<G>() * 4);
     int done = 0;
     auto merges = [&]() __attribute__((always_inline)) {
-      const int nl = uniform(__hip_atomic_load(s_list + kStreamRecs, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
+      const int nl = uniform(__hip_atomic_load(s_list + kStreamRecs, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP));
       if (done >= NH * nl) return;
       const int mt = fresh_tid();
       const int team = mt / kTeam, c = mt % kTeam;
