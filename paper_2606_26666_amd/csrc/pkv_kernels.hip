@@ -11,17 +11,19 @@
 //
 // Work mapping. One workgroup owns one task: one KV head g of one row and a token
 // range [t0, t1). Its W = 8 wavefronts (two per SIMD, one workgroup per compute unit)
-// take the range's 16-token pages round-robin, two pages in flight per wave. MfmaTask forms
-// Q.K^T and P.V on the matrix cores, for every G = Hq / Hkv: lane (r, c) = (lane/16, lane%16)
-// loads 16 bytes, dims 8c..8c+7, of tokens 4i+r, so every load covers four whole 256-byte head
-// rows; K and V pass through LDS into the operand layouts. A task ends with an LDS combine of
-// the W wave states in a fixed order. The one-launch route can give a workgroup KV heads g and
-// g + 1 of one split instead (NH = 2, one page in flight per head; G <= 4), which balances the
-// per-head read rates across workgroups.
+// take the range's 16-token pages round-robin, two pages in flight per wave: lane
+// (r, c) = (lane/16, lane%16) loads 16 bytes, dims 8c..8c+7, of tokens 4i+r, so every load
+// covers four whole 256-byte head rows. For G = Hq / Hkv = 4 and 8, Q.K^T and P.V run on the
+// matrix cores, K and V passing through LDS into the operand layouts (MatrixState); for G = 1
+// and 2 on the vector ALU, from the registers the loads fill (VectorState). A task ends with
+// an LDS combine of the W wave states in a fixed order. The one-launch route can give a
+// workgroup KV heads g and g + 1 of one split instead (NH = 2, one page in flight per head;
+// G <= 4), which balances the per-head read rates across workgroups.
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 
 #include <mutex>
+#include <type_traits>
 
 #include "pkv_internal.h"
 
@@ -46,6 +48,25 @@ __device__ __forceinline__ float dpp(float x) {
   return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xF, 0xF, true));
 }
 
+// Sum over the 16 lanes of a DPP row; every lane of the row receives the same value.
+__device__ __forceinline__ float row_sum16(float x) {
+  x += dpp<0xB1>(x);   // quad_perm [1,0,3,2]
+  x += dpp<0x4E>(x);   // quad_perm [2,3,0,1]
+  x += dpp<0x141>(x);  // row_half_mirror
+  x += dpp<0x140>(x);  // row_mirror
+  return x;
+}
+
+// N = 16: the odd 16-lane rows of a change places with the even rows of b; N = 32: the upper half of
+// a with the lower half of b.
+template <int N>
+__device__ __forceinline__ void swap_rows(float& a, float& b) {
+  const unsigned x = __builtin_bit_cast(unsigned, a), y = __builtin_bit_cast(unsigned, b);
+  const auto r = N == 16 ? __builtin_amdgcn_permlane16_swap(x, y, false, false) : __builtin_amdgcn_permlane32_swap(x, y, false, false);
+  a = __builtin_bit_cast(float, (unsigned)r[0]);
+  b = __builtin_bit_cast(float, (unsigned)r[1]);
+}
+
 __device__ __forceinline__ float ex2(float x) { return __builtin_amdgcn_exp2f(x); }
 
 
@@ -56,6 +77,17 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t page_rsrc(const void* base, in
 }
 
 typedef unsigned v4u __attribute__((ext_vector_type(4)));
+typedef _Float16 h2v __attribute__((ext_vector_type(2)));
+typedef _Float16 h8v __attribute__((ext_vector_type(8)));
+
+// Dot product of eight fp16 pairs in fp32.
+__device__ __forceinline__ float dot8(v4u a, v4u b) {
+  float s = 0.0f;
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+    s = __builtin_amdgcn_fdot2(__builtin_bit_cast(h2v, (unsigned)a[i]), __builtin_bit_cast(h2v, (unsigned)b[i]), s, false);
+  return s;
+}
 
 // Cache policy of the K and V page loads: non-temporal (the nt bit of the buffer
 // instruction's cache-policy operand). A step reads every KV byte once; with the
@@ -600,10 +632,9 @@ __device__ __forceinline__ void finish_task(const DecodeArgs& a, int slot, float
 }
 
 // ---------------------------------------------------------------------------------
-// The task body. Both products run on the matrix cores: the path is 4 flop per byte at G = 4,
-// far below their rate, but the vector form spends its issue slots on dot products and FMAs
-// (G = 4, 32 K tokens: 32.3 against 28.0 us; G = 1 and 2 stream two KV heads per workgroup this
-// way: b4 bimodal at G = 1 139 -> 129 us, b8 Zipf at G = 2 119 -> 106).
+// The task body on the matrix cores (G = 4 and 8): the path is 4 flop per byte at G = 4, far
+// below their rate, but the vector form spends its issue slots on dot products and FMAs (G = 4,
+// 32 K tokens: 32.3 against 28.0 us).
 //
 // Per 16-token page of the task's KV head, one wave computes
 //   S[16 tokens x 16] = K_page[16 x 128] . Q^T[128 x 16]       (4 x mfma 16x16x32 f16)
@@ -625,7 +656,6 @@ __device__ __forceinline__ void finish_task(const DecodeArgs& a, int slot, float
 //   output      dims 16 db + 4 grp + r of head col
 // Every value a lane holds belongs to head col, so the online-softmax max (shared by the
 // four groups of a head, per page) and the rescale are per lane.
-typedef _Float16 h8v __attribute__((ext_vector_type(8)));
 typedef _Float16 h4v __attribute__((ext_vector_type(4)));
 typedef short s4v __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) s4v lds_s4v;
@@ -656,8 +686,9 @@ __device__ __forceinline__ int opaque(int x) {
 // The weights p = 2^(x - m) enter the product scaled by kWeightScale (a power of two, so every
 // value carries it exactly; a wave's l takes it on with its state, and the final division
 // takes it out). P is multiplied as fp16 hi + lo parts, and fp16 ends at 2^-24: scaled, a
-// weight keeps 22 bits down to 2^-28 and is lost only below 2^-39 (unscaled: 2^-14 and 2^-25,
-// where the many small weights of a long row add up to a visible part of the sum).
+// weight keeps 22 bits down to 2^-17 of the largest and below that an absolute error of 2^-39
+// (unscaled: 2^-3 and 2^-25, where the many small weights of a long row add up to a visible part
+// of the sum). A V that is infinite gives a NaN where the lo part is 0 or negative.
 constexpr float kWeightScale = 16384.0f;
 
 struct PageMath {
@@ -734,8 +765,8 @@ struct PageMath {
         m = mp;
       }
     }
-    // P enters the product as fp16 hi + lo parts (p - hi is exact in fp32 and its fp16
-    // rounding leaves ~2^-22 relative), so P.V keeps the fp32 weights' accuracy
+    // P enters the product as fp16 hi + lo parts: p - hi is exact in fp32, and its fp16 rounding
+    // leaves 2^-22 of the weight or 2^-39 of the largest
     const float mref = (m == kNegInf) ? 0.0f : m;
     h4v ph, pl;
 #pragma unroll
@@ -755,6 +786,195 @@ struct PageMath {
   }
 };
 
+// A wave's softmax state of one KV head in the task it is in, with the arithmetic of a page: scores
+// from the page's K and the queries `q` (kQ registers of four words, as load_q leaves them), then
+// accumulate(). dump() leaves the state in LDS.
+template <int G>
+struct MatrixState {
+  typedef v4f Scores;
+  static constexpr int kQ = 4;
+  static constexpr int kStage = kStageUnits;  // 16-byte units of LDS per wave for staged pages
+  float m, l;
+  v4f acc[D / 16];
+
+  __device__ __forceinline__ void reset() {
+    m = kNegInf;
+    l = 0.0f;
+#pragma unroll
+    for (int db = 0; db < D / 16; ++db) acc[db] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+  }
+  // Lane (grp, col): head col, dims [32 c + 8 grp, +8); columns G..15 read past the descriptor
+  // (zeros), so the loads carry no branch. `at`: bytes of this head's queries in it.
+  static __device__ __forceinline__ void load_q(v4u (&q)[kQ], __amdgpu_buffer_rsrc_t r, int at, int tid) {
+    const int grp = (tid & 63) >> 4, col = tid & 15;
+    const int qoff = col < G ? at + (col * D + 8 * grp) * 2 : kOutOfRange;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) q[c] = __builtin_amdgcn_raw_buffer_load_b128(r, qoff, c * 64, 0);
+  }
+  __device__ __forceinline__ void dump(const PageMath& pm, float* acc_at, v2f* ml_at, bool bad, int tid) {
+    const int grp = (tid & 63) >> 4, col = tid & 15;
+    const float lw = pm.over_groups(l, [](float u, float v) { return u + v; }) * kWeightScale;
+    if (col < G) {
+#pragma unroll
+      for (int db = 0; db < D / 16; ++db) *reinterpret_cast<v4f*>(acc_at + col * kHeadPitch + 16 * db + 4 * grp) = acc[db];
+      if (grp == 0) ml_at[col] = v2f{m, bad ? -1.0f : lw};
+    }
+  }
+};
+
+// On the vector ALU: lane (r, c) = (lane / 16, lane % 16) holds dims 8c .. 8c + 7 of tokens 4 i + r
+// as loaded. Partial dot products (v_dot2) meet over the 16 lanes of a row; each row keeps a
+// softmax state of its own (m, l, its lanes' 8 columns of acc), and the four rows meet in dump().
+// Weights stay in fp32 from the exponential to the sum, and a weight times an infinite V is
+// infinite, neither of which the matrix form's fp16 halves can give. As fast in the routes' kernels:
+// four rows at G = 1 128.6 (matrix) and 127.9 us, eight rows at G = 2 105.8 and 105.2; with one
+// head per workgroup and no LDS for pages, rectangular slots of rows of 1500 tokens (Hkv = 32,
+// 8 rows) 43.7 and 28.8; slowest against it at G = 2: 2% to 4% for rows of 16-32 K tokens one by
+// one (78 and 80 us), up to 7% for grids of 16384 short slots (147 and 158).
+template <int G>
+struct VectorState {
+  struct Scores {
+    float x[G][4];
+  };
+  static constexpr int kQ = G;
+  static constexpr int kStage = 64;  // no page is staged: room for the merge's 128 (weight, l) pairs
+  float m[G], l[G], acc[G][8];
+
+  __device__ __forceinline__ void reset() {
+#pragma unroll
+    for (int h = 0; h < G; ++h) {
+      m[h] = kNegInf;
+      l[h] = 0.0f;
+#pragma unroll
+      for (int k = 0; k < 8; ++k) acc[h][k] = 0.0f;
+    }
+  }
+  static __device__ __forceinline__ void load_q(v4u (&q)[kQ], __amdgpu_buffer_rsrc_t r, int at, int tid) {
+#pragma unroll
+    for (int h = 0; h < G; ++h) q[h] = __builtin_amdgcn_raw_buffer_load_b128(r, at + (tid & 15) * 16, h * D * 2, 0);
+  }
+  __device__ __forceinline__ Scores scores(const v4u (&q)[kQ], const v4u (&kr)[4], float scale_log2) const {
+    Scores s;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int h = 0; h < G; ++h) s.x[h][i] = row_sum16(dot8(q[h], kr[i])) * scale_log2;
+    return s;
+  }
+  __device__ __forceinline__ void accumulate(Scores& s, v4u (&vr)[4], int tok0, int t1) {
+    if (tok0 + P > t1) {  // the row's last, partial page: this lane row's token in load i is tok + 4i
+      const int tok = tok0 + ((fresh_tid() & 63) >> 4);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const bool valid = tok + 4 * i < t1;
+#pragma unroll
+        for (int h = 0; h < G; ++h) s.x[h][i] = valid ? s.x[h][i] : kNegInf;
+        const unsigned keep = valid ? ~0u : 0u;  // p is 0 there, but 0 * NaN is not
+        vr[i] &= v4u{keep, keep, keep, keep};
+      }
+    }
+    float mt[G];
+    bool grow = false;
+#pragma unroll
+    for (int h = 0; h < G; ++h) {
+      mt[h] = fmaxf(fmaxf(s.x[h][0], s.x[h][1]), fmaxf(s.x[h][2], s.x[h][3]));
+      grow |= mt[h] > m[h];
+    }
+    if (__builtin_amdgcn_ballot_w64(grow)) {  // rescale only when some running max grows
+#pragma unroll
+      for (int h = 0; h < G; ++h) {
+        if (mt[h] > m[h]) {
+          const float alpha = ex2(m[h] - mt[h]);
+          l[h] *= alpha;
+#pragma unroll
+          for (int k = 0; k < 8; ++k) acc[h][k] *= alpha;
+          m[h] = mt[h];
+        }
+      }
+    }
+    float vf[4][8];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const h8v v = __builtin_bit_cast(h8v, vr[i]);
+#pragma unroll
+      for (int k = 0; k < 8; ++k) vf[i][k] = (float)v[k];
+    }
+#pragma unroll
+    for (int h = 0; h < G; ++h) {
+      const float mref = (m[h] == kNegInf) ? 0.0f : m[h];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float p = ex2(s.x[h][i] - mref);
+        l[h] += p;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) acc[h][k] = __builtin_fmaf(p, vf[i][k], acc[h][k]);
+      }
+    }
+  }
+  // The four rows' states meet: rows 0 and 1 and rows 2 and 3, then the two pairs. An exchange of
+  // two columns leaves one of them with each partner, so the second step has half the columns and
+  // a lane ends with two: every column goes through the operations of a full exchange of rows
+  // (2 G (8 + 2) ds_bpermute per head; G = 2, 256 rows of 64-160 tokens: 200 us against 157).
+  __device__ __forceinline__ void dump(const PageMath&, float* acc_at, v2f* ml_at, bool bad, int tid) {
+    const int lane = tid & 63;
+#pragma unroll
+    for (int h = 0; h < G; ++h) {
+      auto meet = [&](auto swap, auto& from, auto& to) __attribute__((always_inline)) {
+        constexpr int n = sizeof(to) / sizeof(float);
+        float m0 = m[h], m1 = m[h], l0 = l[h], l1 = l[h];
+        swap(m0, m1);
+        swap(l0, l1);
+        const float M = fmaxf(m0, m1);
+        const float Mref = (M == kNegInf) ? 0.0f : M;
+        const float ca = ex2(m0 - Mref);
+        const float cb = ex2(m1 - Mref);
+        l[h] = __builtin_fmaf(cb, l1, ca * l0);
+        m[h] = M;
+#pragma unroll
+        for (int k = 0; k < n; ++k) {
+          float x = from[k], y = from[k + n];
+          swap(x, y);
+          to[k] = __builtin_fmaf(cb, y, ca * x);
+        }
+      };
+      float half[4], quarter[2];
+      meet([](float& a, float& b) { swap_rows<16>(a, b); }, acc[h], half);
+      meet([](float& a, float& b) { swap_rows<32>(a, b); }, half, quarter);
+      const int at = (lane & 15) * 8 + ((lane >> 4) & 1) * 4 + (lane >> 5) * 2;
+      *reinterpret_cast<v2f*>(acc_at + h * kHeadPitch + at) = v2f{quarter[0], quarter[1]};
+    }
+    if (lane == 0) {  // as single floats: from a pair, the compiler loads m[h] and its neighbour as one and spills both
+      float* to = reinterpret_cast<float*>(ml_at);
+#pragma unroll
+      for (int h = 0; h < G; ++h) {
+        to[2 * h] = m[h];
+        to[2 * h + 1] = bad ? -1.0f : l[h];
+      }
+    }
+  }
+};
+
+template <int G>
+constexpr bool on_matrix_cores() { return G >= 4; }
+template <bool MATRIX, int G>
+struct StateSel {
+  typedef VectorState<G> type;
+};
+template <int G>
+struct StateSel<true, G> {
+  typedef MatrixState<G> type;
+};
+template <int G>
+using State = typename StateSel<on_matrix_cores<G>(), G>::type;
+
+// LDS for the staged pages of W waves, in 16-byte units; kernels without it (VectorState stages
+// none) pass a null area.
+template <int G, int W>
+__device__ __forceinline__ v4u* wave_stage(int wave) {
+  if constexpr (on_matrix_cores<G>()) return kv_stage<W>() + wave * kStageUnits;
+  else return nullptr;
+}
+
 // A task body runs in three phases, so that the one-launch route can issue a task's
 // first loads before its plan is known (split_kernel):
 //   begin(row, g, t0, t1)  loads Q and the wave's first 64 page ids
@@ -770,12 +990,12 @@ struct PageMath {
 // per head. Each head's state goes through exactly the operations the one-head body
 // applies to it, in the same order, so its result is bitwise that of the one-head body.
 template <int G, int W, int NH = 1>
-struct MfmaTask {
+struct Task {
   static_assert(G <= 16, "heads fit the 16 MFMA columns");
   static_assert(NH == 1 || NH == 2, "one or two KV heads per task body");
   int row = 0, g = 0, t0 = 0, pg_end = 0, first = 0, npw = 0, ids = 0;  // npw = 0: no task begun
   bool bad = false;
-  v4u qb[NH][4];
+  v4u q[NH][State<G>::kQ];
   // NH = 1: pages j (ka, va) and j + 1 (kb, vb); NH = 2: page j of head g (ka, va) and of
   // head g + 1 (kb, vb)
   v4u ka[4], va[4], kb[4], vb[4];
@@ -786,22 +1006,15 @@ struct MfmaTask {
     t0 = t0_;
     pg_end = uniform((t1_ + P - 1) / P);
     const int lane = threadIdx.x & 63;
-    const int grp = lane >> 4;
-    const int col = lane & 15;
     const int wave = uniform(threadIdx.x >> 6);
     first = uniform(t0 / P + wave);
     npw = uniform(first < pg_end ? (pg_end - first + W - 1) / W : 0);
     bad = false;
-    // Q of the NH * G query heads through one buffer descriptor; lanes past the G heads
-    // (MFMA columns G..15) read at an offset past its end, which returns zeros, so the
-    // loads carry no branch and the page-id load below need not wait for them.
+    // Q of the NH * G query heads through one buffer descriptor, with no branch, so that the
+    // page-id load below need not wait for it
     const __amdgpu_buffer_rsrc_t q_rsrc = page_rsrc(a.q + ((size_t)row * a.Hq + (size_t)g * G) * D, NH * G * D * 2);
 #pragma unroll
-    for (int hh = 0; hh < NH; ++hh) {
-      const int qoff = col < G ? ((hh * G + col) * D + 8 * grp) * 2 : kOutOfRange;
-#pragma unroll
-      for (int c = 0; c < 4; ++c) qb[hh][c] = __builtin_amdgcn_raw_buffer_load_b128(q_rsrc, qoff, c * 64, 0);
-    }
+    for (int hh = 0; hh < NH; ++hh) State<G>::load_q(q[hh], q_rsrc, hh * G * D * 2, threadIdx.x);
     ids = lane < npw ? a.block_table[(size_t)row * a.max_pages_per_row + first + lane * W] : 0;
   }
 
@@ -853,30 +1066,26 @@ struct MfmaTask {
     float* lds_acc = state_acc<G, W, NH>(lds);
     const int lane = threadIdx.x & 63;
     const int wave = uniform(threadIdx.x >> 6);
-    const int grp = lane >> 4;
-    const int col = lane & 15;
-
-    float m[NH], l[NH];
-    v4f acc[NH][D / 16];
+    State<G> st[NH];
 #pragma unroll
-    for (int hh = 0; hh < NH; ++hh) {
-      m[hh] = kNegInf;
-      l[hh] = 0.0f;
-#pragma unroll
-      for (int db = 0; db < D / 16; ++db) acc[hh][db] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
-    }
+    for (int hh = 0; hh < NH; ++hh) st[hh].reset();
     PageMath pm;
-    pm.init(kv_stage<W>() + wave * kStageUnits);
+    if constexpr (on_matrix_cores<G>()) pm.init(wave_stage<G, W>(wave));
 
-    // one page of one head into that head's state (m, l, acc) with its query block qh
-    auto consume = [&](v4u (&kr)[4], v4u (&vr)[4], int k, float& m, float& l, v4f (&acc)[D / 16],
-                       const v4u (&qh)[4]) {
+    // One page of head hh into its state, whose parts are arguments of their own: reached through
+    // the closure alone, the compiler keeps a second copy of acc across the loop (20 registers).
+    auto consume = [&](v4u (&kr)[4], v4u (&vr)[4], int k, int hh, auto& m, auto& l, auto& acc) __attribute__((always_inline)) {
       const int pg = first + k * W;
       const int t1 = pg == pg_end - 1 ? plan.last_t1() : pg_end * P;  // pages before the last are whole
-      pm.stage_k(kr);
-      const v4f sc = pm.scores(qh);
-      pm.stage_v(vr, pg * P, t1);
-      pm.accumulate(sc, a.scale_log2, pg * P, t1, m, l, acc);
+      if constexpr (on_matrix_cores<G>()) {
+        pm.stage_k(kr);
+        const v4f sc = pm.scores(q[hh]);
+        pm.stage_v(vr, pg * P, t1);
+        pm.accumulate(sc, a.scale_log2, pg * P, t1, m, l, acc);
+      } else {
+        auto sc = st[hh].scores(q[hh], kr, a.scale_log2);
+        st[hh].accumulate(sc, vr, pg * P, t1);
+      }
     };
 
     bool dropped = false;
@@ -892,14 +1101,14 @@ struct MfmaTask {
         int j = 0;
         for (; j + 2 < n; j += 2) {
           if ((dropped = plan.dropped())) break;
-          consume(ka, va, k0 + j, m[0], l[0], acc[0], qb[0]);
+          consume(ka, va, k0 + j, 0, st[0].m, st[0].l, st[0].acc);
           issue(a, ka, va, j + 2, true);
-          consume(kb, vb, k0 + j + 1, m[0], l[0], acc[0], qb[0]);
+          consume(kb, vb, k0 + j + 1, 0, st[0].m, st[0].l, st[0].acc);
           issue(a, kb, vb, (j + 3) & 63, j + 3 < n);
         }
         if (dropped) break;
-        consume(ka, va, k0 + j, m[0], l[0], acc[0], qb[0]);
-        if (j + 1 < n) consume(kb, vb, k0 + j + 1, m[0], l[0], acc[0], qb[0]);
+        consume(ka, va, k0 + j, 0, st[0].m, st[0].l, st[0].acc);
+        if (j + 1 < n) consume(kb, vb, k0 + j + 1, 0, st[0].m, st[0].l, st[0].acc);
       } else {
         if (k0 > 0) {
           ids = (k0 + lane < npw) ? a.block_table[(size_t)row * a.max_pages_per_row + first + (k0 + lane) * W] : 0;
@@ -910,29 +1119,20 @@ struct MfmaTask {
         int j = 0;
         for (; j + 1 < n; ++j) {
           if ((dropped = plan.dropped())) break;
-          consume(ka, va, k0 + j, m[0], l[0], acc[0], qb[0]);
+          consume(ka, va, k0 + j, 0, st[0].m, st[0].l, st[0].acc);
           issue(a, ka, va, j + 1, true, 0);
-          consume(kb, vb, k0 + j, m[NH - 1], l[NH - 1], acc[NH - 1], qb[NH - 1]);
+          consume(kb, vb, k0 + j, NH - 1, st[NH - 1].m, st[NH - 1].l, st[NH - 1].acc);
           issue(a, kb, vb, j + 1, true, 1);
         }
         if (dropped) break;
-        consume(ka, va, k0 + j, m[0], l[0], acc[0], qb[0]);
-        consume(kb, vb, k0 + j, m[NH - 1], l[NH - 1], acc[NH - 1], qb[NH - 1]);
+        consume(ka, va, k0 + j, 0, st[0].m, st[0].l, st[0].acc);
+        consume(kb, vb, k0 + j, NH - 1, st[NH - 1].m, st[NH - 1].l, st[NH - 1].acc);
       }
     }
 
-    // wave state per head: m per head (shared by the groups), l summed over the groups, acc
 #pragma unroll
-    for (int hh = 0; hh < NH; ++hh) {
-      const float lw = pm.over_groups(l[hh], [](float u, float v) { return u + v; }) * kWeightScale;
-      if (col < G) {
-#pragma unroll
-        for (int db = 0; db < D / 16; ++db)
-          *reinterpret_cast<v4f*>(lds_acc + ((hh * W + wave) * G + col) * kHeadPitch + 16 * db + 4 * grp) =
-              acc[hh][db];
-        if (grp == 0) lds_ml[(hh * W + wave) * G + col] = v2f{m[hh], bad ? -1.0f : lw};
-      }
-    }
+    for (int hh = 0; hh < NH; ++hh)
+      st[hh].dump(pm, lds_acc + (hh * W + wave) * G * kHeadPitch, lds_ml + (hh * W + wave) * G, bad, threadIdx.x);
     __syncthreads();
   }
 };
@@ -947,7 +1147,7 @@ struct KnownTask {
 template <int G, int W, bool COHERENT, int NH = 1>
 __device__ __forceinline__ void run_split_task(const DecodeArgs& a, int row, int g, int t0, int t1, int slot,
                                                float* lds) {
-  MfmaTask<G, W, NH> body;
+  Task<G, W, NH> body;
   body.begin(a, row, g, t0, t1);
   body.prime(a);
   KnownTask known{t1};
@@ -1484,7 +1684,7 @@ __global__ __launch_bounds__(W * 64) void split_kernel(DecodeArgs a) {
   // the start, so later scalar loads of them do not wait on memory (after the planner,
   // and at the end of the last task).
   asm volatile("" ::"s"(a.q), "s"(a.partials), "s"(gridDim.x));
-  MfmaTask<G, W, NH> body;
+  Task<G, W, NH> body;
   bool begun = false;  // the workgroup's body holds a task begun before the plan
   int plan_ntasks = 0;
   __shared__ int plan_ready;  // wave planner: set once wave 0 has put the plan in LDS
@@ -1621,7 +1821,7 @@ __global__ __launch_bounds__(W * 64) void split_kernel(DecodeArgs a) {
   };
   // Task t (record in rec) on body `bd`, which holds a begun task when `keep`: the loads
   // it began are used if they cover task t, else the task is begun again.
-  auto task = [&](MfmaTask<G, W, NH>& bd, int t, bool keep) __attribute__((always_inline)) {
+  auto task = [&](Task<G, W, NH>& bd, int t, bool keep) __attribute__((always_inline)) {
     const int row = uniform(rec[0]), g = uniform(rec[1]);
     const int t0 = uniform(rec[2]), t1 = uniform(rec[3]);
     if (row < 0 || row >= a.B || g < 0 || g % NH != 0 || g + NH > a.Hkv || t0 < 0 || t1 <= t0 ||
@@ -1649,7 +1849,7 @@ __global__ __launch_bounds__(W * 64) void split_kernel(DecodeArgs a) {
   }
   for (t += NH * gridDim.x; t + NH <= ntasks; t += NH * gridDim.x) {
     fetch(t);
-    MfmaTask<G, W, NH> next;
+    Task<G, W, NH> next;
     task(next, t, false);
   }
   if (FUSED) {  // rows without tasks: their output is zero
@@ -1693,36 +1893,27 @@ __device__ __forceinline__ StreamSlice scalar(const StreamSlice& s) {
   return StreamSlice{uniform(s.row), uniform(s.g), uniform(s.first), uniform(s.npw), uniform(s.pg_end), uniform(s.t1)};
 }
 
-// One head of a wave: its queries, the page in flight and the softmax state.
-struct StreamHead {
-  v4u q[4], kr[4], vr[4];
-  float m, l;
-  v4f acc[D / 16];
+// One head of a wave: its queries, the page in flight and the state.
+template <int G>
+struct StreamHead : State<G> {
+  static constexpr int kQ = State<G>::kQ;
+  v4u q[kQ], kr[4], vr[4];
 
-  __device__ __forceinline__ void reset() {
-    m = kNegInf;
-    l = 0.0f;
-#pragma unroll
-    for (int db = 0; db < D / 16; ++db) acc[db] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
-  }
   // Forgets the loaded values: they are not kept in registers up to here.
   __device__ __forceinline__ void drop() {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) asm volatile("" : "=v"(q[i]), "=v"(kr[i]), "=v"(vr[i]));
-  }
-  // The G query heads of KV head g (MFMA columns G..15 read past the descriptor: zeros).
-  template <int G>
-  __device__ __forceinline__ void load_q(const DecodeArgs& a, int row, int g) {
-    const int tid = fresh_tid();
-    const int grp = (tid & 63) >> 4, col = tid & 15;
-    const __amdgpu_buffer_rsrc_t q_rsrc = page_rsrc(a.q + ((size_t)row * a.Hq + (size_t)g * G) * D, G * D * 2);
-    const int qoff = col < G ? (col * D + 8 * grp) * 2 : kOutOfRange;
+    for (int i = 0; i < kQ; ++i) asm volatile("" : "=v"(q[i]));
 #pragma unroll
-    for (int c = 0; c < 4; ++c) q[c] = __builtin_amdgcn_raw_buffer_load_b128(q_rsrc, qoff, c * 64, 0);
+    for (int i = 0; i < 4; ++i) asm volatile("" : "=v"(kr[i]), "=v"(vr[i]));
+  }
+  // The G query heads of KV head g.
+  __device__ __forceinline__ void queries(const DecodeArgs& a, int row, int g) {
+    State<G>::load_q(q, page_rsrc(a.q + ((size_t)row * a.Hq + (size_t)g * G) * D, G * D * 2), 0, fresh_tid());
   }
   // Loads of page `phys` of KV head g; unless live through an empty descriptor (zeros, no
   // memory access), so that every path issues the same loads and the wait counts stay exact.
   // An id outside the pool sets *bad (LDS); page 0 is read in its place.
+  template <bool K = true, bool V = true>
   __device__ __forceinline__ void issue(const DecodeArgs& a, int kv_off, int g, int phys, bool live, int* bad) {
     const int tok_b = a.Hkv * D * 2;  // bytes between consecutive tokens
     if (live && (unsigned)phys >= (unsigned)a.num_pages) *bad = 1;
@@ -1733,23 +1924,11 @@ struct StreamHead {
     const __amdgpu_buffer_rsrc_t kr_rsrc = page_rsrc(reinterpret_cast<const char*>(a.k) + at, bytes);
     const __amdgpu_buffer_rsrc_t vr_rsrc = page_rsrc(reinterpret_cast<const char*>(a.v) + at, bytes);
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; K && i < 4; ++i)
       kr[i] = __builtin_amdgcn_raw_buffer_load_b128(kr_rsrc, kv_off, g * D * 2 + i * 4 * tok_b, kKvPolicy);
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; V && i < 4; ++i)
       vr[i] = __builtin_amdgcn_raw_buffer_load_b128(vr_rsrc, kv_off, g * D * 2 + i * 4 * tok_b, kKvPolicy);
-  }
-  // The wave's state of a finished task into LDS.
-  template <int G>
-  __device__ __forceinline__ void dump(const PageMath& pm, float* acc_at, v2f* ml_at, bool bad) const {
-    const int lane = fresh_tid() & 63;
-    const int grp = lane >> 4, col = lane & 15;
-    const float lw = pm.over_groups(l, [](float u, float v) { return u + v; }) * kWeightScale;
-    if (col < G) {
-#pragma unroll
-      for (int db = 0; db < D / 16; ++db) *reinterpret_cast<v4f*>(acc_at + col * kHeadPitch + 16 * db + 4 * grp) = acc[db];
-      if (grp == 0) ml_at[col] = v2f{m, bad ? -1.0f : lw};
-    }
   }
 };
 
@@ -1762,10 +1941,20 @@ __device__ __forceinline__ void vm_wait() {
   __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
 }
 
+// LDS of a stream's workgroup that its staged pages, the plan's row weights and the merges share.
+template <int G, int W>
+constexpr int stream_stage_units() {
+  constexpr int pages = W * State<G>::kStage, merge = (merge_lds_floats<G, 1, W * 64>() + 3) / 4;
+  constexpr int rows = (kMaxFusedPlanBatch + 1 + 3) / 4;
+  return pages > merge ? (pages > rows ? pages : rows) : (merge > rows ? merge : rows);
+}
+
 template <int G, int W, bool FUSED, bool PLAN>
 __global__ __launch_bounds__(W * 64) void stream_kernel(DecodeArgs a) {
   constexpr int NH = 2;
-  __shared__ v4u stage[W * kStageUnits];             // staged pages; the plan's row weights; merge scratch
+  constexpr int kStage = State<G>::kStage;            // per wave
+  constexpr int kStageAll = stream_stage_units<G, W>();
+  __shared__ v4u stage[kStageAll];                   // staged pages; the plan's row weights; merge scratch
   __shared__ float s_state[lds_floats<G, W, NH>()];  // the unit's wave states
   __shared__ int s_bad[5 * W];                       // page-error flags: unit i's at (i % 4) * W, the hint's last
   __shared__ int s_rec[kStreamRecs * 8];
@@ -1775,13 +1964,12 @@ __global__ __launch_bounds__(W * 64) void stream_kernel(DecodeArgs a) {
   __shared__ int p_wave[W];
   __shared__ long long p_w64[2 * W];
   __shared__ int p_wmax[W];
-  static_assert(merge_lds_floats<G, 1, W * 64>() <= W * kStageUnits * 4, "the merge's scratch fits the staging area");
   const PlanLds PL{p_len, p_off, p_wave, p_w64, p_wmax, reinterpret_cast<int*>(stage)};
   const int lane = threadIdx.x & 63;
   const int wave = uniform(threadIdx.x >> 6);
-  v4u* st = stage + wave * kStageUnits;
+  v4u* st = stage + wave * kStage;
   PageMath pm;
-  pm.init(st);
+  if constexpr (on_matrix_cores<G>()) pm.init(st);
   const int kv_off = opaque((lane >> 4) * (a.Hkv * D * 2) + (lane & 15) * 16);  // this lane's piece of a page's head
 
   auto slice = [&](int row, int g, int t0, int t1) {
@@ -1801,7 +1989,7 @@ __global__ __launch_bounds__(W * 64) void stream_kernel(DecodeArgs a) {
                                                s.npw > k0 ? (s.pg_end - s.first - k0 * W) * 4 : 0);
     return (int)__builtin_amdgcn_raw_buffer_load_b32(r, tid * (W * 4), 0, 0);
   };
-  StreamHead h[NH];
+  StreamHead<G> h[NH];
   StreamSlice cur, nxt{0, 0, 0, 0, 0, 0}, nn;
   int ids = 0, ids_nxt = 0, ids_nn = 0;
   auto start = [&](const StreamSlice& s, int id, int* bad) {  // first pages of a unit
@@ -1843,7 +2031,7 @@ __global__ __launch_bounds__(W * 64) void stream_kernel(DecodeArgs a) {
       nxt = slice(hr, hg, ht0, h1);
       ids_nxt = load_ids(nxt, 0);
 #pragma unroll
-      for (int hh = 0; hh < NH; ++hh) h[hh].template load_q<G>(a, nxt.row, nxt.g + hh);
+      for (int hh = 0; hh < NH; ++hh) h[hh].queries(a, nxt.row, nxt.g + hh);
     }
     if (by_wave && threadIdx.x < 64) plan_compute_wave(a.plan, PL, blockIdx.x == 0, n_raw);
     if (primed) start(nxt, __builtin_amdgcn_readlane(ids_nxt, 0), s_bad + 4 * W + wave);
@@ -1985,7 +2173,7 @@ __global__ __launch_bounds__(W * 64) void stream_kernel(DecodeArgs a) {
       if (!keep) {
         ids_nxt = load_ids(nxt, 0);
 #pragma unroll
-        for (int hh = 0; hh < NH; ++hh) h[hh].template load_q<G>(a, nxt.row, nxt.g + hh);
+        for (int hh = 0; hh < NH; ++hh) h[hh].queries(a, nxt.row, nxt.g + hh);
       } else if (lane == 0) {
         s_bad[wave] = s_bad[4 * W + wave];
       }
@@ -2031,22 +2219,36 @@ __global__ __launch_bounds__(W * 64) void stream_kernel(DecodeArgs a) {
         const int phys = more ? own : other;
 #pragma unroll
         for (int hh = 0; hh < NH; ++hh) {
-          v4f sc = {0.0f, 0.0f, 0.0f, 0.0f};
+          // The next page's loads go out as soon as the registers are free: all of them once K and V
+          // are staged, or K's after the scores and V's after the sums.
+          constexpr bool kStaged = on_matrix_cores<G>();
+          typename State<G>::Scores sc{};
           if (live) {
-            pm.stage_k(h[hh].kr);
-            sc = pm.scores(h[hh].q);
-            pm.stage_v(h[hh].vr, pg * P, t1);
+            if constexpr (kStaged) {
+              pm.stage_k(h[hh].kr);
+              sc = pm.scores(h[hh].q);
+              pm.stage_v(h[hh].vr, pg * P, t1);
+            } else {
+              sc = h[hh].scores(h[hh].q, h[hh].kr, a.scale_log2);
+            }
           }
-          if (!more) h[hh].template load_q<G>(a, nxt.row, nxt.g + hh);
-          h[hh].issue(a, kv_off, (more ? cur.g : nxt.g) + hh, phys, more || nxt.npw > 0, more ? bad : bad_nxt);
-          if (live) pm.accumulate(sc, a.scale_log2, pg * P, t1, h[hh].m, h[hh].l, h[hh].acc);
+          if (!more) h[hh].queries(a, nxt.row, nxt.g + hh);
+          const int g = (more ? cur.g : nxt.g) + hh;
+          const bool next_live = more || nxt.npw > 0;
+          h[hh].template issue<true, kStaged>(a, kv_off, g, phys, next_live, more ? bad : bad_nxt);
+          if constexpr (kStaged) {
+            if (live) pm.accumulate(sc, a.scale_log2, pg * P, t1, h[hh].m, h[hh].l, h[hh].acc);
+          } else {
+            if (live) h[hh].accumulate(sc, h[hh].vr, pg * P, t1);
+          }
+          if (!kStaged) h[hh].template issue<false, true>(a, kv_off, g, phys, next_live, more ? bad : bad_nxt);
         }
       } while (k < cur.npw);
       lds_barrier();  // the unit before this one has been combined
 #pragma unroll
       for (int hh = 0; hh < NH; ++hh)
-        h[hh].template dump<G>(pm, state_acc<G, W, NH>(s_state) + (hh * W + wave) * G * kHeadPitch,
-                               state_ml<G, W, NH>(s_state) + (hh * W + wave) * G, *bad != 0);
+        h[hh].dump(pm, state_acc<G, W, NH>(s_state) + (hh * W + wave) * G * kHeadPitch,
+                   state_ml<G, W, NH>(s_state) + (hh * W + wave) * G, *bad != 0, fresh_tid());
       lds_barrier();
       const int* r = s_rec + i * 8;
       const int row = uniform(r[0]), g = uniform(r[1]), ns = uniform(r[5]);
@@ -2094,7 +2296,7 @@ __global__ __launch_bounds__(W * 64) void stream_kernel(DecodeArgs a) {
       lds_barrier();
       const int nl = uniform(s_list[kStreamRecs]);
       // Several left: side by side. One or two: by the whole workgroup, one round of loads each.
-      constexpr int kHeads = merge_lds_floats<G, NH, W * 64>() <= W * kStageUnits * 4 ? NH : 1;  // per merge_group
+      constexpr int kHeads = merge_lds_floats<G, NH, W * 64>() <= kStageAll * 4 ? NH : 1;  // per merge_group
       const int from = nl - uniform(done) / NH > 2 ? nl : uniform(done) / NH;
       if (from == nl) merges();
       for (int j = 0; j < nl; ++j) {
@@ -2167,12 +2369,13 @@ __global__ __launch_bounds__(W * 64) void rect_kernel(DecodeArgs a) {
 // combined. The hardware deals the workgroups out, so what else a slot spends outside its page
 // reads is hidden only by other workgroups on the compute unit: a wave keeps one page in
 // flight (as in the stream above), which with the wave states laid over the staged pages holds
-// a workgroup to 128 registers and 72 KB of LDS, two of them per compute unit.
+// a workgroup to 128 registers and 72 KB of LDS, two of them per compute unit (on the vector ALU
+// to 80 registers: three).
 template <int G, int W, int NH>
-__global__ __launch_bounds__(W * 64, 4) void rect_dense_kernel(DecodeArgs a) {
-  __shared__ v4u stage[W * kStageUnits];
+__global__ __launch_bounds__(W * 64, on_matrix_cores<G>() ? 4 : 6) void rect_dense_kernel(DecodeArgs a) {
+  constexpr int kPages = on_matrix_cores<G>() ? W * kStageUnits : 0, kStates = (lds_floats<G, W>() + 3) / 4;
+  __shared__ v4u stage[kPages > kStates ? kPages : kStates];
   __shared__ int s_bad[NH * W];
-  static_assert(lds_floats<G, W>() <= W * kStageUnits * 4, "the wave states fit the staging area");
   float* state = reinterpret_cast<float*>(stage);
   const int slot = NH * (int)blockIdx.x;
   const int g = slot % a.Hkv;
@@ -2184,17 +2387,17 @@ __global__ __launch_bounds__(W * 64, 4) void rect_dense_kernel(DecodeArgs a) {
   const int lane = threadIdx.x & 63;
   const int wave = uniform(threadIdx.x >> 6);
   PageMath pm;
-  pm.init(stage + wave * kStageUnits);
+  if constexpr (on_matrix_cores<G>()) pm.init(stage + wave * kStageUnits);
   const int kv_off = opaque((lane >> 4) * (a.Hkv * D * 2) + (lane & 15) * 16);
   const int pg_end = (r.t1 + P - 1) / P, first = r.t0 / P + wave;
   const int npw = first < pg_end ? (pg_end - first + W - 1) / W : 0;
   const int32_t* idrow = a.block_table + (size_t)r.row * a.max_pages_per_row + first;
   auto load_ids = [&](int k0) { return lane < npw - k0 ? idrow[(size_t)(k0 + lane) * W] : 0; };
   if (lane < NH) s_bad[lane * W + wave] = 0;
-  StreamHead h;
+  StreamHead<G> h;
   const int first_ids = load_ids(0);
   h.issue(a, kv_off, g, __builtin_amdgcn_readlane(first_ids, 0), npw > 0, s_bad + wave);
-  h.template load_q<G>(a, r.row, g);
+  h.queries(a, r.row, g);
 #pragma clang loop unroll(disable)
   for (int hh = 0; hh < NH; ++hh) {
     h.reset();
@@ -2203,19 +2406,31 @@ __global__ __launch_bounds__(W * 64, 4) void rect_dense_kernel(DecodeArgs a) {
     for (int k = 0; k < npw; ++k) {
       const int pg = first + k * W;
       const int end = pg == pg_end - 1 ? r.t1 : pg_end * P;  // pages before the last are whole
-      pm.stage_k(h.kr);
-      pm.stage_v(h.vr, pg * P, end);
       const bool more = k + 1 < npw;
-      if (more && ((k + 1) & 63) == 0) ids = load_ids(k + 1);
-      const int phys = __builtin_amdgcn_readlane(ids, (k + 1) & 63), phys0 = __builtin_amdgcn_readlane(first_ids, 0);
-      h.issue(a, kv_off, more ? g + hh : g + hh + 1, more ? phys : phys0, more || hh + 1 < NH,
-              s_bad + (more || hh + 1 == NH ? hh : hh + 1) * W + wave);
-      pm.accumulate(pm.scores(h.q), a.scale_log2, pg * P, end, h.m, h.l, h.acc);
+      auto next = [&](auto k_too, auto v_too) __attribute__((always_inline)) {
+        const int phys = __builtin_amdgcn_readlane(ids, (k + 1) & 63), phys0 = __builtin_amdgcn_readlane(first_ids, 0);
+        h.template issue<decltype(k_too)::value, decltype(v_too)::value>(
+            a, kv_off, more ? g + hh : g + hh + 1, more ? phys : phys0, more || hh + 1 < NH,
+            s_bad + (more || hh + 1 == NH ? hh : hh + 1) * W + wave);
+      };
+      if constexpr (on_matrix_cores<G>()) {
+        pm.stage_k(h.kr);
+        pm.stage_v(h.vr, pg * P, end);
+        if (more && ((k + 1) & 63) == 0) ids = load_ids(k + 1);
+        next(std::true_type{}, std::true_type{});
+        pm.accumulate(pm.scores(h.q), a.scale_log2, pg * P, end, h.m, h.l, h.acc);
+      } else {
+        if (more && ((k + 1) & 63) == 0) ids = load_ids(k + 1);
+        auto sc = h.scores(h.q, h.kr, a.scale_log2);
+        next(std::true_type{}, std::false_type{});
+        h.accumulate(sc, h.vr, pg * P, end);
+        next(std::false_type{}, std::true_type{});
+      }
     }
-    if (hh + 1 < NH) h.template load_q<G>(a, r.row, g + hh + 1);
+    if (hh + 1 < NH) h.queries(a, r.row, g + hh + 1);
     lds_barrier();  // every wave is done with its staged page
-    h.template dump<G>(pm, state_acc<G, W>(state) + wave * G * kHeadPitch, state_ml<G, W>(state) + wave * G,
-                       s_bad[hh * W + wave] != 0);
+    h.dump(pm, state_acc<G, W>(state) + wave * G * kHeadPitch, state_ml<G, W>(state) + wave * G,
+           s_bad[hh * W + wave] != 0, fresh_tid());
     lds_barrier();
     finish_task<G, W, false>(a, slot + hh, state, nullptr, fresh_tid());
     lds_barrier();
@@ -2408,28 +2623,45 @@ hipError_t launch_decode_g(const DecodeArgs& a, int mode, int grid, hipStream_t 
   if (mode == 2) {
     const int rows = a.n_rows > 0 ? a.n_rows : a.B;
     const int slots = rows * a.Hkv * a.S;
-    // A slot of at most two pages per wave is a chain of round trips more than a read. Beyond one
-    // slot per compute unit a workgroup then runs the chains of two KV heads as one (16 splits of
-    // rows of 2048 tokens: 512 slots 14.4 -> 12.5 us, 640 18.8 -> 18.3, 1408 33.9 -> 28.2; of 4096
-    // tokens 19.9 -> 17.5, 25.9 -> 25.9, 47.7 -> 41.3). Longer slots are balanced better one by
-    // one (four rows of 17-32 K tokens twice: 108 against 102), and from 1536 slots on the dense
-    // kernel is the faster (rows of 1024 tokens: 1536 slots 21.4 against 22.7, 8192 76 against 94).
     const int64_t tiles = ((int64_t)a.max_pages * P + a.tile_tokens - 1) / a.tile_tokens;
     const int64_t slot_pages = (tiles + a.S - 1) / a.S * (a.tile_tokens / P);
-    // Many slots are small ones (each row has S of them): from six per compute unit on, two
-    // workgroups a unit with one page in flight per wave beat one with two (13 rows of up to
-    // 8250 tokens, 1664 slots: 46 against 48 us; 21 rows of up to 39 K, 1344 slots: 146 against
-    // 139), and from twelve rounds of them on two slots per workgroup beat one (60 rows of up
-    // to 4096 tokens, 7680 slots: 103 against 112 us; 2560 slots: 86 against 82).
+    const bool even = a.Hkv % 2 == 0;
+    bool pairs, dense;  // two heads per workgroup; the dense kernel
+    if constexpr (on_matrix_cores<G>()) {
+      // A slot of at most two pages per wave is a chain of round trips more than a read. Beyond one
+      // slot per compute unit a workgroup then runs the chains of two KV heads as one (16 splits of
+      // rows of 2048 tokens: 512 slots 14.4 -> 12.5 us, 640 18.8 -> 18.3, 1408 33.9 -> 28.2; of 4096
+      // tokens 19.9 -> 17.5, 25.9 -> 25.9, 47.7 -> 41.3). Longer slots are balanced better one by
+      // one (four rows of 17-32 K tokens twice: 108 against 102), and from 1536 slots on the dense
+      // kernel is the faster (rows of 1024 tokens: 1536 slots 21.4 against 22.7, 8192 76 against 94).
+      // Many slots are small ones (each row has S of them): from six per compute unit on, two
+      // workgroups a unit with one page in flight per wave beat one with two (13 rows of up to
+      // 8250 tokens, 1664 slots: 46 against 48 us; 21 rows of up to 39 K, 1344 slots: 146 against
+      // 139), and from twelve rounds of them on two slots per workgroup beat one (60 rows of up
+      // to 4096 tokens, 7680 slots: 103 against 112 us; 2560 slots: 86 against 82).
+      dense = slots >= 6 * 256;
+      pairs = even && (dense ? slots >= 12 * 512 : G <= 4 && slots > 256 && slot_pages <= 2 * W);
+    } else if (G == 1) {
+      // Without staged pages two one-head workgroups fit a compute unit. Pairs pay as soon as one
+      // round of those does not hold the slots (Hkv = 32, 1024 slots of rows of 1500 tokens 11.4 ->
+      // 9.9 us, 32 rows 122.6 -> 93.7; 512 slots of 24 K tokens 17.0 against 21.4). An odd head
+      // left over: short slots dense from six per compute unit on (Hkv = 3, 64 rows of 1500
+      // tokens 28.6 -> 24.8 us, 24 K tokens 115 against 122).
+      pairs = even && slots > 2 * 256;
+      dense = !even && slots >= 6 * 256 && slot_pages <= 2 * W;
+    } else {
+      // G = 2: one by one, dense (three workgroups a unit) from six slots per compute unit on
+      // (Hkv = 16: 2048 slots of rows of 1500 tokens 23.8 -> 22.4 us, 16384 of 400 tokens 83 -> 78;
+      // pairs of heads in the dense kernel 83 and 141 against 79 and 138, rows of 64 tokens 52
+      // against 44), with an odd head short slots only (Hkv = 3, 32 rows of 24 K tokens 124 against 118).
+      pairs = false;
+      dense = slots >= 6 * 256 && (even || slot_pages <= 2 * W);
+    }
     hipError_t e;
-    if (G <= 4 && a.Hkv % 2 == 0 && slots > 256 && slots < 6 * 256 && slot_pages <= 2 * W)
-      e = launch(rect_kernel<G, W, G <= 4 ? 2 : 1>, slots / 2, W * 64, s, start, nullptr, a);
-    else if (slots < 6 * 256)
-      e = launch(rect_kernel<G, W, 1>, slots, W * 64, s, start, nullptr, a);
-    else if (a.Hkv % 2 == 0 && slots >= 12 * 512)
-      e = launch(rect_dense_kernel<G, W, 2>, slots / 2, W * 64, s, start, nullptr, a);
-    else
-      e = launch(rect_dense_kernel<G, W, 1>, slots, W * 64, s, start, nullptr, a);
+    if (dense && pairs) e = launch(rect_dense_kernel<G, W, on_matrix_cores<G>() ? 2 : 1>, slots / 2, W * 64, s, start, nullptr, a);
+    else if (dense) e = launch(rect_dense_kernel<G, W, 1>, slots, W * 64, s, start, nullptr, a);
+    else if (pairs) e = launch(rect_kernel<G, W, G == 1 || G == 4 ? 2 : 1>, slots / 2, W * 64, s, start, nullptr, a);
+    else e = launch(rect_kernel<G, W, 1>, slots, W * 64, s, start, nullptr, a);
     if (e != hipSuccess) return e;
     return launch(merge_kernel<G, true>, rows * a.Hkv, kMergeThreads, s, nullptr, stop, a);
   }

@@ -194,6 +194,19 @@ inline int __builtin_amdgcn_update_dpp(int old, int x, int ctrl, int row_mask, i
   if (!((row_mask >> (l >> 4)) & 1)) return old;
   return src >= 0 ? emu::from<int>(all, src) : (bound_ctrl ? 0 : old);
 }
+namespace emu {
+typedef unsigned v2 __attribute__((ext_vector_type(2)));
+// The odd groups of n lanes of a change places with the even ones of b.
+inline v2 permlane_swap(unsigned a, unsigned b, int n) {
+  const uint64_t* all = exchange(a | (uint64_t)b << 32, "permlane_swap");
+  const int l = lane();
+  return l & n ? v2{(unsigned)(all[l ^ n] >> 32), b} : v2{a, (unsigned)all[l ^ n]};
+}
+}  // namespace emu
+inline emu::v2 __builtin_amdgcn_permlane16_swap(unsigned a, unsigned b, bool, bool) { return emu::permlane_swap(a, b, 16); }
+inline emu::v2 __builtin_amdgcn_permlane32_swap(unsigned a, unsigned b, bool, bool) { return emu::permlane_swap(a, b, 32); }
+template <typename V>
+inline float __builtin_amdgcn_fdot2(V a, V b, float c, bool) { return std::fma((float)a[1], (float)b[1], std::fma((float)a[0], (float)b[0], c)); }
 inline float __builtin_amdgcn_exp2f(float x) { return std::exp2(x); }
 inline void __builtin_amdgcn_s_waitcnt(int) {}
 inline void __builtin_amdgcn_s_sleep(int) { emu::yield(); }
@@ -208,7 +221,6 @@ inline __amdgpu_buffer_rsrc_t __builtin_amdgcn_make_buffer_rsrc(void* p, short, 
   return {(char*)p, (uint32_t)bytes};
 }
 namespace emu {
-typedef unsigned v2 __attribute__((ext_vector_type(2)));
 typedef unsigned v4 __attribute__((ext_vector_type(4)));
 template <typename T>
 inline T load(__amdgpu_buffer_rsrc_t r, int off, int soff) {

@@ -71,3 +71,50 @@ def test_bad_page_of_a_hinted_unit_is_kept(program, hq, hkv, page, order):
         assert a.error_bits == PAGE_ID and a.counters_left == 0, (n, a.error_bits)
         assert np.all(a.out[0] == 0), n
         close(a.out[1:], ref[1:], n)
+
+
+def route_args(route, hkv):
+    return dict(S=3) if route == "rect" else dict(bucket_tokens=32) if route == "buckets" else {}
+
+
+@pytest.mark.parametrize("route", ["plan_decode", "fused", "separate", "rect"])
+@pytest.mark.parametrize("hq,hkv", [(2, 2), (4, 2), (3, 3), (6, 3)])
+def test_infinite_values_stay_infinite(program, hq, hkv, route):
+    """One query head per KV head, or two: an infinite V with a positive weight is an infinite output,
+    whatever the weight's bits, and no other dimension sees it."""
+    c = Call([70, 33], hq=hq, hkv=hkv, seed=5)
+    at = {(0, 0, 3): np.inf, (0, 37, 64): -np.inf, (1, 32, 127): np.inf}  # row, token, dim
+    for (row, tok, dim), x in at.items():
+        c.v[c.bt[row, tok // 16], tok % 16, :, dim] = x
+    (a,), _ = c.run(program, route, params(hkv, split_max=3), **route_args(route, hkv))
+    seen = np.zeros(a.out.shape, dtype=bool)
+    for (row, _, dim), x in at.items():
+        assert np.all(a.out[row, :, dim] == x), (row, dim, a.out[row, :, dim])
+        seen[row, :, dim] = True
+    v, c.v = c.v, np.where(np.isinf(c.v), np.float16(0), c.v)
+    ref = reference(c)
+    assert np.all(np.isfinite(a.out[~seen]))
+    close(np.where(seen, ref, a.out), ref)
+
+
+@pytest.mark.parametrize("route", ["plan_decode", "separate", "rect"])
+@pytest.mark.parametrize("hq,hkv", HEADS)
+def test_small_weights(program, hq, hkv, route):
+    """One token has the largest weight and V = 0, 62 others about 2^-30 of it and V = 65504: the
+    output is their share, 3.4e-3. With one or two query heads the weights are fp32 throughout. With
+    more they enter the product as fp16 halves of 2^14 times the weight, with an error of at most
+    2^-39 of the largest weight each."""
+    n = 63
+    c = Call([n], hq=hq, hkv=hkv, seed=6)
+    c.k[:], c.q[:] = 0, 0
+    c.q[:, :, 0] = 1
+    pages = c.bt[0, : (n + 15) // 16]
+    c.k[pages, :, :, 0] = np.float16(-20.95)
+    c.v[pages] = 65504
+    c.k[pages[0], 0, :, 0] = 0
+    c.v[pages[0], 0] = 0
+    (a,), _ = c.run(program, route, params(hkv, split_max=2), **route_args(route, hkv))
+    w = np.exp(np.float64(np.float16(-20.95)))
+    ref = 62 * w * 65504 / (1 + 62 * w)
+    bound = ref * (2.0 ** -11 + 2.0 ** -20) + (0 if hq // hkv <= 2 else 62 * 65504 * 2.0 ** -39)
+    assert np.abs(a.out.astype(np.float64) - ref).max() <= bound
