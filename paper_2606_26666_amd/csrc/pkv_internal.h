@@ -64,6 +64,7 @@ struct DecodeArgs {
   int32_t max_pages_per_row;
   int32_t B, Hq, Hkv;
   int32_t max_tasks;
+  int32_t slots;        // stream behind pkv_plan: workgroups the device holds at once
   int32_t S;            // rectangular route only
   int32_t tile_tokens;  // rectangular route only
   int32_t n_rows;       // rectangular route: rows named in row_ids (0: rows 0..B-1)

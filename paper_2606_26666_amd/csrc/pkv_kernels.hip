@@ -967,11 +967,10 @@ struct StateSel<true, G> {
 template <int G>
 using State = typename StateSel<on_matrix_cores<G>(), G>::type;
 
-// LDS for the staged pages of W waves, in 16-byte units; kernels without it (VectorState stages
-// none) pass a null area.
+// The staged pages of W waves; null where none are staged.
 template <int G, int W>
-__device__ __forceinline__ v4u* wave_stage(int wave) {
-  if constexpr (on_matrix_cores<G>()) return kv_stage<W>() + wave * kStageUnits;
+__device__ __forceinline__ v4u* task_stage() {
+  if constexpr (on_matrix_cores<G>()) return kv_stage<W>();
   else return nullptr;
 }
 
@@ -979,8 +978,9 @@ __device__ __forceinline__ v4u* wave_stage(int wave) {
 // first loads before its plan is known (split_kernel):
 //   begin(row, g, t0, t1)  loads Q and the wave's first 64 page ids
 //   prime()                issues the loads of the wave's first two pages (waits for the ids)
-//   run(last_t1)           the page loop, then the wave states in LDS (finish_task and
-//                          the fused route combine them into the task's partial state)
+//   run(plan, lds, stage)  the page loop (pages staged at `stage`), then the wave states in
+//                          `lds` (finish_task and the fused route combine them into the
+//                          task's partial state)
 // covers(row, g, t0, t1) tells whether a begun task read exactly what task (row, g, t0,
 // t1) reads in those phases: the same row, head and first token and the same page
 // count. t1 itself only masks tokens of the last page, which run() applies.
@@ -1061,7 +1061,7 @@ struct Task {
   }
 
   template <typename PlanView>
-  __device__ __forceinline__ void run(const DecodeArgs& a, PlanView& plan, float* lds) {
+  __device__ __forceinline__ void run(const DecodeArgs& a, PlanView& plan, float* lds, v4u* stage) {
     v2f* lds_ml = state_ml<G, W, NH>(lds);
     float* lds_acc = state_acc<G, W, NH>(lds);
     const int lane = threadIdx.x & 63;
@@ -1070,7 +1070,7 @@ struct Task {
 #pragma unroll
     for (int hh = 0; hh < NH; ++hh) st[hh].reset();
     PageMath pm;
-    if constexpr (on_matrix_cores<G>()) pm.init(wave_stage<G, W>(wave));
+    if constexpr (on_matrix_cores<G>()) pm.init(stage + wave * kStageUnits);
 
     // One page of head hh into its state, whose parts are arguments of their own: reached through
     // the closure alone, the compiler keeps a second copy of acc across the loop (20 registers).
@@ -1151,7 +1151,7 @@ __device__ __forceinline__ void run_split_task(const DecodeArgs& a, int row, int
   body.begin(a, row, g, t0, t1);
   body.prime(a);
   KnownTask known{t1};
-  body.run(a, known, lds);
+  body.run(a, known, lds, task_stage<G, W>());
   finish_task<G, W, COHERENT, NH>(a, slot, lds, nullptr, threadIdx.x);
 }
 
@@ -1735,7 +1735,7 @@ __global__ __launch_bounds__(W * 64) void split_kernel(DecodeArgs a) {
       body.prime(a);  // nothing to issue when no task was begun (npw = 0)
       if (begun && kSpecRun) {
         SpecTask spec{a.plan, PL, &plan_ready, NH * (int)blockIdx.x, hr, hg, h0, (h1 + P - 1) / P};
-        body.run(a, spec, lds);
+        body.run(a, spec, lds, task_stage<G, W>());
         // The run ended with a workgroup barrier: wave 0's plan is visible to every wave.
         // Every wave's verdict is the same; most waves formed it in the page loop, so a
         // kept run finishes with the hint's record and the plan's t1, no lookup.
@@ -1834,7 +1834,7 @@ __global__ __launch_bounds__(W * 64) void split_kernel(DecodeArgs a) {
       bd.prime(a);
     }
     KnownTask known{t1};
-    bd.run(a, known, lds);
+    bd.run(a, known, lds, task_stage<G, W>());
     finish(t, row, g);
   };
   // The first task is the only one a speculative start can have begun (and run); later
@@ -1878,6 +1878,24 @@ __global__ __launch_bounds__(W * 64) void split_kernel(DecodeArgs a) {
 // Every task goes through exactly the operations of the one-task kernels in their order
 // (eight waves taking its pages round-robin, the same combine and merge), so results are
 // bitwise the same.
+// Whether `tasks` tasks run as a stream of KV-head pairs, `slots` (one per compute unit)
+// at a time, rather than on the one-task kernels. The stream goes through ceil(tasks / 2 slots)
+// rounds of units of two tasks each, the one-task kernels through ceil(tasks / slots) rounds
+// with a gap after each; an odd number of rounds leaves the stream half a round behind.
+// - One head per workgroup as the alternative: two rounds are one of units (the layers of 16
+//   rows 258 -> 253 us; at G = 8, whose units combine twice the states, 57 -> 59), three are
+//   two (608 tasks: 106 against 119), and from four on the gaps decide (1024 tasks 149 -> 145,
+//   62 -> 59 for short rows; G = 8: 51 -> 48 at 1024 tasks, 250 -> 155 at 8192).
+// - KV-head pairs as the alternative (`paired`: the one-launch route at G < 8): they have the
+//   same rounds and a shorter start, and win while rounds are few (1888 tasks 95.5 against
+//   96.5, 1024 tasks 276 against 278); from eight tasks per slot on the gaps decide (3200
+//   tasks 104 -> 101 and 59 -> 45 for short rows, 8192 tasks 175 -> 135).
+template <typename T>
+__host__ __device__ __forceinline__ bool stream_pays(int G, T tasks, int slots, bool paired) {
+  if (paired) return tasks >= 8 * (T)slots;
+  return tasks > 3 * (T)slots || (G < 8 && tasks > (T)slots && tasks <= 2 * (T)slots);  // rounds >= 4, or 2
+}
+
 constexpr int kStreamRecs = 32;  // unit records a workgroup holds in LDS
 
 struct StreamRec {
@@ -1949,6 +1967,52 @@ constexpr int stream_stage_units() {
   return pages > merge ? (pages > rows ? pages : rows) : (merge > rows ? merge : rows);
 }
 
+// One task of a list behind pkv_plan by itself, as split_kernel runs it: two pages in flight per
+// wave, then the state, the count and, for the last of its row and KV head, the merge.
+template <int G, int W, bool FUSED>
+__device__ __forceinline__ void lone_task(const DecodeArgs& a, int t, const TaskRec& r, float* state, v4u* stage, int* last) {
+  if (r.row < 0 || r.row >= a.B || r.g < 0 || r.g >= a.Hkv || r.t0 < 0 || r.t1 <= r.t0 ||
+      r.t1 > a.max_pages_per_row * P) {  // not a task of a valid plan: flag and skip
+    if (threadIdx.x == 0) atomicOr(a.err, (unsigned)PKV_DEVERR_TASK);
+    return;
+  }
+  Task<G, W> body;
+  body.begin(a, r.row, r.g, r.t0, r.t1);
+  body.prime(a);
+  KnownTask known{r.t1};
+  body.run(a, known, state, stage);
+  if (!FUSED) {
+    finish_task<G, W, false>(a, t, state, nullptr, fresh_tid());
+  } else {
+    const int off = uniform(a.split_offsets[r.row]);
+    int ns = uniform(a.split_offsets[r.row + 1]) - off;
+    const bool fits = off >= 0 && ns >= 1 && (long long)(off + ns) * a.Hkv <= a.max_tasks;
+    uint16_t* out = a.out + ((size_t)r.row * a.Hq + (size_t)r.g * G) * D;
+    finish_task<G, W, true>(a, t, state, fits && ns == 1 ? out : nullptr, fresh_tid());
+    if (!fits || ns > 1) {
+      if (!fits) {
+        if (threadIdx.x == 0) atomicOr(a.err, (unsigned)PKV_DEVERR_TASK);
+        ns = 0;  // never reached by the counter: no merge from inconsistent offsets
+      }
+      vm_wait<0>();  // this wave's stores are acknowledged
+      __syncthreads();
+      if (threadIdx.x == 0) {
+        const int prev = __hip_atomic_fetch_add(&a.counters[r.row * a.Hkv + r.g], 1, __ATOMIC_RELAXED,
+                                                __HIP_MEMORY_SCOPE_AGENT);
+        *last = prev == ns - 1;
+        if (*last) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+      }
+      __syncthreads();
+      if (*last) {
+        merge_group<G, W * 64, true>(slots_rsrc(a, slot_floats<G>() * 4), off * a.Hkv + r.g, a.Hkv, ns, out,
+                                     reinterpret_cast<float*>(stage));
+        if (threadIdx.x == 0) a.counters[r.row * a.Hkv + r.g] = 0;
+      }
+    }
+  }
+  __syncthreads();
+}
+
 template <int G, int W, bool FUSED, bool PLAN>
 __global__ __launch_bounds__(W * 64) void stream_kernel(DecodeArgs a) {
   constexpr int NH = 2;
@@ -1959,12 +2023,41 @@ __global__ __launch_bounds__(W * 64) void stream_kernel(DecodeArgs a) {
   __shared__ int s_bad[5 * W];                       // page-error flags: unit i's at (i % 4) * W, the hint's last
   __shared__ int s_rec[kStreamRecs * 8];
   __shared__ int s_list[kStreamRecs + 1];            // records whose (row, head pair) this workgroup merges; count
+  __shared__ int s_last;                             // one task by itself: whether it was the last of its states
   __shared__ int p_len[PLAN ? kMaxFusedPlanBatch : 1];
   __shared__ int p_off[PLAN ? kMaxFusedPlanBatch + 1 : 1];
   __shared__ int p_wave[W];
   __shared__ long long p_w64[2 * W];
   __shared__ int p_wmax[W];
   const PlanLds PL{p_len, p_off, p_wave, p_w64, p_wmax, reinterpret_cast<int*>(stage)};
+  auto zero_rows = [&]() {
+    if (FUSED) {  // rows without tasks: their output is zero
+      for (int i = blockIdx.x; i < a.B; i += gridDim.x) {
+        const bool empty = PLAN ? p_off[i + 1] == p_off[i] : a.split_offsets[i + 1] == a.split_offsets[i];
+        if (empty) zero_row<G>(a, i);
+      }
+    }
+  };
+  // The host chose this kernel by the tasks it expects of the batch. Where the list is shorter
+  // (empty or short rows) and its tasks are better run one by one, they are: the stream's units
+  // would leave half of the compute units without work (64 rows, 58 of them empty, one plan and
+  // two layers: G = 8 77 -> 58 us, G = 1 70 -> 54).
+  // Ahead of all else, or the stream would carry what both need in registers of its own.
+  int ntasks = 0;
+  const int grid = gridDim.x;
+  if (!PLAN) {
+    ntasks = uniform(*a.num_tasks);
+    if (ntasks > a.max_tasks) ntasks = a.max_tasks;
+  }
+  if (!PLAN && __builtin_expect(!stream_pays(G, ntasks, a.slots, false), 0)) {
+    for (int t = blockIdx.x; t < ntasks; t += grid) {
+      const int* tp = reinterpret_cast<const int*>(a.tasks + t);
+      lone_task<G, W, FUSED>(a, t, TaskRec{uniform(tp[0]), uniform(tp[1]), uniform(tp[2]), uniform(tp[3]), uniform(tp[4])},
+                             s_state, stage, &s_last);
+    }
+    zero_rows();
+    return;
+  }
   const int lane = threadIdx.x & 63;
   const int wave = uniform(threadIdx.x >> 6);
   v4u* st = stage + wave * kStage;
@@ -2003,7 +2096,6 @@ __global__ __launch_bounds__(W * 64) void stream_kernel(DecodeArgs a) {
   // This workgroup's units: blockIdx.x, then tb + i * ts for 0 < i < n. Unit u is tasks
   // 2u and 2u + 1.
   int tb, ts, n;
-  const int grid = gridDim.x;
   if (PLAN) {
     // While the plan is formed, the waves start the unit listed at this workgroup's index by
     // the previous launch (split_kernel's speculative start): its first pages are kept if the
@@ -2035,7 +2127,6 @@ __global__ __launch_bounds__(W * 64) void stream_kernel(DecodeArgs a) {
     }
     if (by_wave && threadIdx.x < 64) plan_compute_wave(a.plan, PL, blockIdx.x == 0, n_raw);
     if (primed) start(nxt, __builtin_amdgcn_readlane(ids_nxt, 0), s_bad + 4 * W + wave);
-    int ntasks;
     if (by_wave) {
       lds_barrier();
       ntasks = plan_wave_tasks(a.plan, PL, blockIdx.x == 0);
@@ -2057,8 +2148,6 @@ __global__ __launch_bounds__(W * 64) void stream_kernel(DecodeArgs a) {
       n = __builtin_amdgcn_readlane(b, 1) - tb;
     }
   } else {
-    int ntasks = uniform(*a.num_tasks);
-    if (ntasks > a.max_tasks) ntasks = a.max_tasks;
     const int nunits = ntasks / NH;
     tb = blockIdx.x;
     ts = grid;
@@ -2317,12 +2406,7 @@ __global__ __launch_bounds__(W * 64) void stream_kernel(DecodeArgs a) {
     }
     for (int hh = 0; hh < NH; ++hh) h[hh].drop();
   }
-  if (FUSED) {  // rows without tasks: their output is zero
-    for (int i = blockIdx.x; i < a.B; i += gridDim.x) {
-      const bool empty = PLAN ? p_off[i + 1] == p_off[i] : a.split_offsets[i + 1] == a.split_offsets[i];
-      if (empty) zero_row<G>(a, i);
-    }
-  }
+  zero_rows();
 }
 
 // Rectangular grid: slot (j*S + s)*Hkv + g is split s of KV head g of launch row j, which is
@@ -2592,29 +2676,20 @@ hipError_t launch(K kernel, int grid, int threads, hipStream_t s, hipEvent_t sta
   return hipGetLastError();
 }
 
-// Whether about `tasks` tasks run as a stream of KV-head pairs, `slots` (one per compute unit)
-// at a time, rather than on the one-task kernels. The stream goes through ceil(tasks / 2 slots)
-// rounds of units of two tasks each, the one-task kernels through ceil(tasks / slots) rounds
-// with a gap after each; an odd number of rounds leaves the stream half a round behind.
-// - One head per workgroup as the alternative: two rounds are one of units (the layers of 16
-//   rows 258 -> 253 us; at G = 8, whose units combine twice the states, 57 -> 59), three are
-//   two (608 tasks: 106 against 119), and from four on the gaps decide (1024 tasks 149 -> 145,
-//   62 -> 59 for short rows; G = 8: 51 -> 48 at 1024 tasks, 250 -> 155 at 8192).
-// - KV-head pairs as the alternative (`paired`: the one-launch route at G < 8): they have the
-//   same rounds and a shorter start, and win while rounds are few (1888 tasks 95.5 against
-//   96.5, 1024 tasks 276 against 278); from eight tasks per slot on the gaps decide (3200
-//   tasks 104 -> 101 and 59 -> 45 for short rows, 8192 tasks 175 -> 135).
+// Whether a launch goes to the stream kernel, by the tasks the host expects.
 bool streams(int G, int Hkv, int max_tasks, int64_t tasks, int slots, bool paired) {
-  if (Hkv % 2 != 0 || max_tasks < 2) return false;
-  if (paired) return tasks >= 8 * slots;
-  const int64_t rounds = (tasks + slots - 1) / slots;
-  return rounds >= 4 || (rounds == 2 && G < 8);
+  return Hkv % 2 == 0 && max_tasks >= 2 && stream_pays(G, tasks, slots, paired);
 }
 
 template <int G, int W, bool FUSED, bool PLAN>
 int stream_slots() {
   static const int r = resident_blocks((const void*)stream_kernel<G, W, FUSED, PLAN>, W * 64);
   return r;
+}
+
+DecodeArgs with_slots(DecodeArgs a, int slots) {
+  a.slots = slots;
+  return a;
 }
 
 template <int G, int W>
@@ -2685,19 +2760,20 @@ hipError_t launch_decode_g(const DecodeArgs& a, int mode, int grid, hipStream_t 
     return launch(split_kernel<G, W, true, true>, grid < resident ? grid : resident, W * 64, s, start, stop, a);
   }
   // A task list made elsewhere: its length is on the device only. The default target's
-  // four splits per row and KV head stand for it.
+  // four splits per row and KV head stand for it, and the stream kernel looks at the list's
+  // own length again.
   const int64_t expected = (int64_t)4 * a.B * a.Hkv;
   if (mode == 1) {
     const int r = stream_slots<G, W, true, false>();
     if (streams(G, a.Hkv, grid, expected, r, false))
-      return launch(stream_kernel<G, W, true, false>, grid / 2 < r ? grid / 2 : r, W * 64, s, start, stop, a);
+      return launch(stream_kernel<G, W, true, false>, grid < r ? grid : r, W * 64, s, start, stop, with_slots(a, r));
     static const int resident = resident_blocks((const void*)split_kernel<G, W, true, false>, W * 64);
     return launch(split_kernel<G, W, true, false>, grid < resident ? grid : resident, W * 64, s, start, stop, a);
   }
   hipError_t e;
   const int r = stream_slots<G, W, false, false>();
   if (streams(G, a.Hkv, grid, expected, r, false)) {
-    e = launch(stream_kernel<G, W, false, false>, grid / 2 < r ? grid / 2 : r, W * 64, s, start, nullptr, a);
+    e = launch(stream_kernel<G, W, false, false>, grid < r ? grid : r, W * 64, s, start, nullptr, with_slots(a, r));
   } else {
     static const int resident = resident_blocks((const void*)split_kernel<G, W, false, false>, W * 64);
     e = launch(split_kernel<G, W, false, false>, grid < resident ? grid : resident, W * 64, s, start, nullptr, a);

@@ -118,3 +118,23 @@ def test_small_weights(program, hq, hkv, route):
     ref = 62 * w * 65504 / (1 + 62 * w)
     bound = ref * (2.0 ** -11 + 2.0 ** -20) + (0 if hq // hkv <= 2 else 62 * 65504 * 2.0 ** -39)
     assert np.abs(a.out.astype(np.float64) - ref).max() <= bound
+
+
+@pytest.mark.parametrize("route", ["fused", "separate"])
+@pytest.mark.parametrize("hq,hkv", HEADS)
+@pytest.mark.parametrize("lens", [[0, 0, 0, 0, 70, 0], [90, 0, 0, 1, 0, 0], [70, 400, 0, 0, 0, 0], [33] * 5 + [0]])
+def test_short_lists_where_long_ones_stream(program, route, hq, hkv, lens):
+    """Six rows are expected to have 48 tasks or more, so the stream kernel is launched; empty and
+    short rows leave one to six rounds of them on two workgroups, which run one by one where a stream
+    would leave a workgroup idle. The same bits as from the one-task kernels (many workgroups)."""
+    c = Call([lens, lens], hq=hq, hkv=hkv, seed=7)
+    p = params(hkv, split_max=3, target=12)
+    for order in SCHEDULES:
+        answers, launched = c.run(program, route, p, order=order, compute_units=2)
+        assert any(k.startswith("stream_kernel") for k in kernels(launched)), launched
+        one, launched = c.run(program, route, p, compute_units=64)
+        assert any(k.startswith("split_kernel") for k in kernels(launched)), launched
+        for a, b in zip(answers, one):
+            assert a.error_bits == 0 and a.counters_left == 0
+            assert np.array_equal(a.out.view(np.uint16), b.out.view(np.uint16))
+        close(answers[0].out, reference(c))
