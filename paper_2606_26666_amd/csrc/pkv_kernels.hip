@@ -566,7 +566,7 @@ __device__ __forceinline__ void merge_columns(__amdgpu_buffer_rsrc_t pr, int slo
 // store share their banks: 0.9 instead of 0.3 us per state of two KV heads).
 // `direct`: the task is its row's only split, so its state is the merged state: the output
 // goes there at once (the arithmetic of a one-split merge: weight 1, sums started at +0) and
-// no state is stored. Threads tid, tid + NT, ... take the columns.
+// no state is stored. Threads tid, tid + NT, ... take the columns. `heads`: how many of the NH.
 constexpr int kHeadPitch = D + 4;
 
 template <int G, int W, int NH = 1>
@@ -579,11 +579,12 @@ template <int G, int W, int NH = 1>
 __device__ __forceinline__ float* state_acc(float* lds) { return lds + 2 * NH * W * G; }
 
 template <int G, int W, bool COHERENT, int NH = 1>
-__device__ __forceinline__ void finish_task(const DecodeArgs& a, int slot, float* lds, uint16_t* direct, int tid) {
+__device__ __forceinline__ void finish_task(const DecodeArgs& a, int slot, float* lds, uint16_t* direct, int tid,
+                                            int heads = NH) {
   constexpr int SB = slot_floats<G>() * 4;
   constexpr int E4H = G * D / 4;  // float4 columns per head
   const __amdgpu_buffer_rsrc_t pr = slots_rsrc(a, SB);
-  for (int e4g = tid; e4g < NH * E4H; e4g += W * 64) {
+  for (int e4g = tid; e4g < heads * E4H; e4g += W * 64) {
     const int hh = e4g / E4H;
     const int e4 = e4g - hh * E4H;
     const int h = (e4 * 4) / D;
@@ -2023,6 +2024,7 @@ __global__ __launch_bounds__(W * 64) void stream_kernel(DecodeArgs a) {
   __shared__ int s_bad[5 * W];                       // page-error flags: unit i's at (i % 4) * W, the hint's last
   __shared__ int s_rec[kStreamRecs * 8];
   __shared__ int s_list[kStreamRecs + 1];            // records whose (row, head pair) this workgroup merges; count
+  __shared__ int s_apart;                            // the stream left units out that are not pairs
   __shared__ int s_last;                             // one task by itself: whether it was the last of its states
   __shared__ int p_len[PLAN ? kMaxFusedPlanBatch : 1];
   __shared__ int p_off[PLAN ? kMaxFusedPlanBatch + 1 : 1];
@@ -2041,7 +2043,7 @@ __global__ __launch_bounds__(W * 64) void stream_kernel(DecodeArgs a) {
   // The host chose this kernel by the tasks it expects of the batch. Where the list is shorter
   // (empty or short rows) and its tasks are better run one by one, they are: the stream's units
   // would leave half of the compute units without work (64 rows, 58 of them empty, one plan and
-  // two layers: G = 8 77 -> 58 us, G = 1 70 -> 54).
+  // two layers: G = 8 77 -> 54 us, G = 1 70 -> 52).
   // Ahead of all else, or the stream would carry what both need in registers of its own.
   int ntasks = 0;
   const int grid = gridDim.x;
@@ -2085,9 +2087,9 @@ __global__ __launch_bounds__(W * 64) void stream_kernel(DecodeArgs a) {
   StreamHead<G> h[NH];
   StreamSlice cur, nxt{0, 0, 0, 0, 0, 0}, nn;
   int ids = 0, ids_nxt = 0, ids_nn = 0;
-  auto start = [&](const StreamSlice& s, int id, int* bad) {  // first pages of a unit
+  auto start = [&](const StreamSlice& s, int id, int* bad, int heads) {  // first pages of a unit
 #pragma unroll
-    for (int hh = 0; hh < NH; ++hh) h[hh].issue(a, kv_off, s.g + hh, id, s.npw > 0, bad);
+    for (int hh = 0; hh < NH; ++hh) h[hh].issue(a, kv_off, s.g + hh, id, s.npw > 0 && hh < heads, bad);
   };
   bool primed = false;  // h and ids_nxt hold the hinted first unit's start
   int ht0 = 0;
@@ -2126,7 +2128,7 @@ __global__ __launch_bounds__(W * 64) void stream_kernel(DecodeArgs a) {
       for (int hh = 0; hh < NH; ++hh) h[hh].queries(a, nxt.row, nxt.g + hh);
     }
     if (by_wave && threadIdx.x < 64) plan_compute_wave(a.plan, PL, blockIdx.x == 0, n_raw);
-    if (primed) start(nxt, __builtin_amdgcn_readlane(ids_nxt, 0), s_bad + 4 * W + wave);
+    if (primed) start(nxt, __builtin_amdgcn_readlane(ids_nxt, 0), s_bad + 4 * W + wave, NH);
     if (by_wave) {
       lds_barrier();
       ntasks = plan_wave_tasks(a.plan, PL, blockIdx.x == 0);
@@ -2148,7 +2150,7 @@ __global__ __launch_bounds__(W * 64) void stream_kernel(DecodeArgs a) {
       n = __builtin_amdgcn_readlane(b, 1) - tb;
     }
   } else {
-    const int nunits = ntasks / NH;
+    const int nunits = (ntasks + NH - 1) / NH;  // an odd last task is a unit by itself
     tb = blockIdx.x;
     ts = grid;
     n = tb < nunits ? (nunits - 1 - tb) / ts + 1 : 0;
@@ -2167,10 +2169,16 @@ __global__ __launch_bounds__(W * 64) void stream_kernel(DecodeArgs a) {
     return u;
   };
 
-  for (int c0 = 0; c0 < n; c0 += kStreamRecs) {  // one stream per kStreamRecs units
+  // One stream per kStreamRecs units. A list behind pkv_plan need not be a plan's: units whose two
+  // tasks are not KV heads g and g + 1 (g even) of one split are left out of their stream and
+  // follow it in two more, of their first and of their second tasks, one head at a time.
+  int apart = 0;  // 0: pairs, 1 and 2: tasks 2u and 2u + 1 of the other units
+  for (int c0 = 0; c0 < n;) {
     const int nc = min(kStreamRecs, n - c0);
+    const int heads = PLAN || apart == 0 ? NH : 1;
+    if (!PLAN && threadIdx.x == 0 && apart == 0) s_apart = 0;
     if (wave == 0 && lane < nc) {  // their records
-      const int t = NH * unit_of(c0 + lane);
+      const int t = NH * unit_of(c0 + lane) + (!PLAN && apart == 2);
       StreamRec r;
       int split = 0;
       if (PLAN) {
@@ -2178,14 +2186,23 @@ __global__ __launch_bounds__(W * 64) void stream_kernel(DecodeArgs a) {
         r = StreamRec{k.row, k.g, k.t0, k.t1, p_off[k.row], p_off[k.row + 1] - p_off[k.row]};
         split = k.split;
       } else {
-        const int* tp = reinterpret_cast<const int*>(a.tasks + t);
+        const int first = t / NH * NH;
+        const bool two = first + 1 < ntasks;
+        const int* tp = reinterpret_cast<const int*>(a.tasks + first);
+        const int* tq = tp + (two ? 5 : 0);
+        StreamRec q{tq[0], tq[1], tq[3], tq[4], 0, 0};  // both tasks at once: one round trip
         r = StreamRec{tp[0], tp[1], tp[3], tp[4], 0, 0};
-        // its partner has to be the next KV head's task of the same split, as in every plan
-        const bool pair = tp[5] == r.row && tp[6] == r.g + 1 && tp[8] == r.t0 && tp[9] == r.t1;
-        if (!pair || r.row < 0 || r.row >= a.B || r.g < 0 || r.g % NH != 0 || r.g + NH > a.Hkv || r.t0 < 0 ||
-            r.t1 <= r.t0 || r.t1 > a.max_pages_per_row * P) {  // not tasks of a valid plan: flag and skip
+        const bool pair = two & (q.row == r.row) & (q.g == r.g + 1) & (r.g % NH == 0) & (q.t0 == r.t0) & (q.t1 == r.t1);
+        if (!pair && apart == 0) s_apart = 1;
+        if (t > first) r = q;
+        const bool mine = apart == 0 ? pair : !pair && t < ntasks;
+        if (!mine) r.row = -1;
+        if (mine && (r.row < 0 || r.row >= a.B || r.g < 0 || r.g + heads > a.Hkv || r.t0 < 0 || r.t1 <= r.t0 ||
+                     r.t1 > a.max_pages_per_row * P)) {  // not a task of this batch: flag and skip
           atomicOr(a.err, (unsigned)PKV_DEVERR_TASK);
           r.row = -1;
+        }
+        if (r.row < 0) {
         } else if (FUSED) {
           r.off = a.split_offsets[r.row];
           r.ns = a.split_offsets[r.row + 1] - r.off;
@@ -2207,6 +2224,7 @@ __global__ __launch_bounds__(W * 64) void stream_kernel(DecodeArgs a) {
     }
     if (threadIdx.x == 0) s_list[kStreamRecs] = 0;
     lds_barrier();
+    const bool left_out = !PLAN && uniform(s_apart) != 0;
 
     auto slice_of = [&](int i) {  // an empty slice past the stream's end and for a skipped unit
       const int* r = s_rec + min(i, nc - 1) * 8;
@@ -2219,12 +2237,15 @@ __global__ __launch_bounds__(W * 64) void stream_kernel(DecodeArgs a) {
     // and tb_ were counted in the last odd and the last even unit's epilogue, na and nb the
     // counts read.
     int s1 = -1, s2 = -1, ta = -1, tb_ = -1, na = 0, nb = 0;
+    // KV heads g and g + 1 (g even) have one count, in which (behind pkv_plan) each head's task is one.
+    constexpr int kTasks = PLAN ? 1 : NH;
+    const int counted = PLAN ? 1 : heads;
     auto count = [&](int i) {
-      return __hip_atomic_fetch_add(&a.counters[s_rec[i * 8] * a.Hkv + s_rec[i * 8 + 1]], 1, __ATOMIC_RELAXED,
+      return __hip_atomic_fetch_add(&a.counters[s_rec[i * 8] * a.Hkv + s_rec[i * 8 + 1] / NH * NH], counted, __ATOMIC_RELAXED,
                                     __HIP_MEMORY_SCOPE_AGENT);
     };
     auto list = [&](int i, int seen) {  // the count says that it was its row's last state
-      if (i >= 0 && seen == s_rec[i * 8 + 5] - 1) {
+      if (i >= 0 && seen == kTasks * s_rec[i * 8 + 5] - counted) {
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");  // before any wave reads the states
         const int at = s_list[kStreamRecs];  // other waves may be reading: the entry, then the count
         __hip_atomic_store(s_list + at, i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -2244,7 +2265,7 @@ __global__ __launch_bounds__(W * 64) void stream_kernel(DecodeArgs a) {
       const int team = mt / kTeam, c = mt % kTeam;
       for (; done < NH * nl; ++done) {
         const int* r = s_rec + s_list[done / NH] * 8;
-        const int row = uniform(r[0]), g = uniform(r[1]) + done % NH, off = uniform(r[4]), ns = uniform(r[5]);
+        const int row = uniform(r[0]), g = uniform(r[1]) / NH * NH + done % NH, off = uniform(r[4]), ns = uniform(r[5]);
         const bool mine = done % kTeams == team && ns <= kColRuns * kMergeRun;
         if (__builtin_amdgcn_ballot_w64(mine) == 0) continue;
         merge_columns<G, true>(pr, off * a.Hkv + g, a.Hkv, mine ? ns : 0, ns, c,
@@ -2262,12 +2283,12 @@ __global__ __launch_bounds__(W * 64) void stream_kernel(DecodeArgs a) {
       if (!keep) {
         ids_nxt = load_ids(nxt, 0);
 #pragma unroll
-        for (int hh = 0; hh < NH; ++hh) h[hh].queries(a, nxt.row, nxt.g + hh);
+        for (int hh = 0; hh < NH; ++hh) h[hh].queries(a, nxt.row, nxt.g + min(hh, heads - 1));
       } else if (lane == 0) {
         s_bad[wave] = s_bad[4 * W + wave];
       }
       ids_nn = load_ids(nn, 0);
-      if (!keep) start(nxt, __builtin_amdgcn_readlane(ids_nxt, 0), s_bad + wave);
+      if (!keep) start(nxt, __builtin_amdgcn_readlane(ids_nxt, 0), s_bad + wave, heads);
       vm_wait<0>();  // on every path, or the compiler would drain the stream at each unit for ids_nn
     }
     for (int i = 0; i < nc; ++i) {
@@ -2321,9 +2342,9 @@ __global__ __launch_bounds__(W * 64) void stream_kernel(DecodeArgs a) {
               sc = h[hh].scores(h[hh].q, h[hh].kr, a.scale_log2);
             }
           }
-          if (!more) h[hh].queries(a, nxt.row, nxt.g + hh);
+          if (!more) h[hh].queries(a, nxt.row, nxt.g + min(hh, heads - 1));
           const int g = (more ? cur.g : nxt.g) + hh;
-          const bool next_live = more || nxt.npw > 0;
+          const bool next_live = (more || nxt.npw > 0) && hh < heads;
           h[hh].template issue<true, kStaged>(a, kv_off, g, phys, next_live, more ? bad : bad_nxt);
           if constexpr (kStaged) {
             if (live) pm.accumulate(sc, a.scale_log2, pg * P, t1, h[hh].m, h[hh].l, h[hh].acc);
@@ -2358,7 +2379,8 @@ __global__ __launch_bounds__(W * 64) void stream_kernel(DecodeArgs a) {
       const int ct = fresh_tid() - (kCols <= W * 32 && (i & 1) ? W * 32 : 0);
       if (row >= 0 && ct >= 0)
         finish_task<G, W, FUSED, NH>(a, uniform(r[6]), s_state,
-                                     FUSED && ns == 1 ? a.out + ((size_t)row * a.Hq + (size_t)g * G) * D : nullptr, ct);
+                                     FUSED && ns == 1 ? a.out + ((size_t)row * a.Hq + (size_t)g * G) * D : nullptr, ct,
+                                     heads);
       if (FUSED) merges();
     }
     if (PLAN && wave == W - 1 && lane < nc) {  // the units' tasks in the task list (off the stream's way)
@@ -2390,7 +2412,7 @@ __global__ __launch_bounds__(W * 64) void stream_kernel(DecodeArgs a) {
       if (from == nl) merges();
       for (int j = 0; j < nl; ++j) {
         const int* r = s_rec + s_list[j] * 8;
-        const int row = uniform(r[0]), g = uniform(r[1]), off = uniform(r[4]), ns = uniform(r[5]);
+        const int row = uniform(r[0]), g = uniform(r[1]) / NH * NH, off = uniform(r[4]), ns = uniform(r[5]);
         if (j < from && ns <= kColRuns * kMergeRun) continue;
         for (int hh = 0; hh < NH; hh += kHeads) {
           lds_barrier();
@@ -2405,6 +2427,12 @@ __global__ __launch_bounds__(W * 64) void stream_kernel(DecodeArgs a) {
       lds_barrier();  // every wave has read its last unit's record: the next stream's may be written
     }
     for (int hh = 0; hh < NH; ++hh) h[hh].drop();
+    if (left_out && apart < 2) {
+      ++apart;
+    } else {
+      apart = 0;
+      c0 += kStreamRecs;
+    }
   }
   zero_rows();
 }

@@ -32,7 +32,7 @@ def compiler():
 
 def build(folder, csrc=CSRC):
     """The program of the sources in `csrc` (seconds)."""
-    flags = [compiler(), "-std=c++17", "-O1", "-fno-pie", "-ffp-contract=off", "-w", "-I", DEVICE, "-I", csrc]
+    flags = [compiler(), "-std=c++17", "-O2", "-fno-pie", "-ffp-contract=off", "-w", "-I", DEVICE, "-I", csrc]
     units = [(os.path.join(csrc, "pkv_kernels.hip"), "kernels"), (os.path.join(csrc, "pkv_capi.cpp"), "capi"),
              (os.path.join(DEVICE, "emu.cpp"), "emu"), (os.path.join(DEVICE, "main.cpp"), "main")]
     objs, jobs = [], []

@@ -138,3 +138,87 @@ def test_short_lists_where_long_ones_stream(program, route, hq, hkv, lens):
             assert a.error_bits == 0 and a.counters_left == 0
             assert np.array_equal(a.out.view(np.uint16), b.out.view(np.uint16))
         close(answers[0].out, reference(c))
+
+
+def own_list(lens, hkv, splits, apart, rng):
+    """A task list in a plan's order (row, split, KV head) with the caller's own ranges: rows named in
+    `apart` are cut at other tokens for every KV head, the others alike."""
+    tasks, offsets = [], [0]
+    for row, n in enumerate(lens):
+        ns = min(splits, n)
+        cuts = []
+        for h in range(hkv):
+            if h == 0 or row in apart:
+                c = sorted(rng.choice(np.arange(1, n), size=ns - 1, replace=False).tolist()) if ns > 1 else []
+                c = [x // 16 * 16 for x in c] if len({x // 16 for x in c} - {0}) == len(c) else [16 * (i + 1) for i in range(ns - 1)]
+            cuts.append([0] + c + [n])
+        for s in range(ns):
+            tasks += [(row, h, s, cuts[h][s], cuts[h][s + 1]) for h in range(hkv)]
+        offsets.append(offsets[-1] + ns)
+    return np.array(tasks, dtype=np.int32), np.array(offsets, dtype=np.int32)
+
+
+@pytest.mark.parametrize("order", [ASCENDING, DESCENDING])
+@pytest.mark.parametrize("route", ["fused", "separate"])
+@pytest.mark.parametrize("hq,hkv,splits", [(2, 2, 3), (4, 2, 1), (16, 4, 3), (16, 2, 2), (8, 2, 70)])
+def test_lists_of_the_callers_own(program, route, hq, hkv, splits, order):
+    """Task lists whose neighbours are not KV heads g and g + 1 of one range, in some rows or in all:
+    the stream runs those tasks one head at a time, with the bits of the one-task kernels."""
+    long = splits > 64
+    lens = [1200, 1300] if long else [100 + (13 * i) % 60 for i in range(40 if splits == 1 else 14)]
+    c = Call(lens, hq=hq, hkv=hkv, seed=8)
+    rng = np.random.Generator(np.random.PCG64(8))
+    for apart in ([1], range(len(lens)), [0, 2, 13, 33]):
+        given = own_list(lens, hkv, splits, set(apart), rng)
+        p = params(hkv, split_max=max(splits, 4))
+        (a,), launched = c.run(program, route, p, given=given, order=order, compute_units=2)
+        assert any(k.startswith("stream_kernel") for k in kernels(launched)), launched
+        (b,), launched = c.run(program, route, p, given=given, compute_units=512)
+        assert any(k.startswith("split_kernel") for k in kernels(launched)), launched
+        assert a.error_bits == b.error_bits == 0 and a.counters_left == 0
+        assert np.array_equal(a.out.view(np.uint16), b.out.view(np.uint16))
+        close(a.out, reference(c), route)
+
+
+@pytest.mark.parametrize("cut", [1, 2, 3])
+def test_a_list_cut_short(program, cut):
+    """The two-kernel route stores the state of every task that is listed, an odd last one too."""
+    lens = [120] * 12
+    c = Call(lens, hq=8, hkv=2, seed=9)
+    tasks, offsets = own_list(lens, 2, 2, set(), np.random.Generator(np.random.PCG64(9)))
+    keep = len(tasks) - cut
+    (a,), launched = c.run(program, "separate", params(2), given=(tasks, offsets), num_tasks=keep, compute_units=2)
+    assert any(k.startswith("stream_kernel") for k in kernels(launched)), launched
+    missing = {(r, h) for r, h, *_ in tasks[keep:].tolist()}
+    ref = reference(c).reshape(12, 2, 4, 128)
+    out = a.out.reshape(12, 2, 4, 128)
+    for row in range(12):
+        for h in range(2):
+            if (row, h) not in missing:
+                close(out[row, h], ref[row, h], (row, h))
+
+
+@pytest.mark.parametrize("compute_units", [2, 64])
+@pytest.mark.parametrize("route", ["fused", "separate"])
+def test_records_that_are_no_tasks_are_flagged(program, route, compute_units):
+    """Rows, heads and ranges outside the batch, as one record of a pair and as both; split_offsets
+    past the capacity: flagged, nothing outside the buffers touched, and the rows without one right."""
+    lens = [120] * 12
+    c = Call(lens, hq=8, hkv=2, seed=10)
+    tasks, offsets = own_list(lens, 2, 2, set(), np.random.Generator(np.random.PCG64(9)))
+    ref = reference(c)
+    for at, word, value in [(4, 0, 99), (5, 0, -1), (9, 1, 2), (8, 1, -3), (12, 3, -16), (13, 4, 1 << 20), (20, 4, 0)]:
+        for both in (False, True):
+            bad = tasks.copy()
+            bad[at, word] = value
+            if both:
+                bad[at ^ 1, word] = value + (word == 1)
+            (a,), _ = c.run(program, route, params(2), given=(bad, offsets), compute_units=compute_units)
+            assert a.error_bits & TASK, (at, word)
+            ok = [r for r in range(12) if r != tasks[at, 0]]
+            close(a.out[ok], ref[ok], (at, word, both))
+    wrong = offsets.copy()
+    wrong[6:] += 1 << 24
+    (a,), _ = c.run(program, route, params(2), given=(tasks, wrong), compute_units=compute_units)
+    assert a.error_bits & TASK
+    close(a.out[:5], ref[:5])

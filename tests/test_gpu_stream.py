@@ -1,7 +1,7 @@
 """The kernels for launches of many tasks: the stream of KV-head pairs (one-launch, fused and
 two-kernel routes) and the dense rectangular grid. The one-launch route streams from 2048 tasks
 on (G = 8: from 769), the routes behind pkv_plan where 4 * B * Hkv is more than 768, or more
-than 256 and up to 512 (G < 8), so a small batch with a large task target is planned and
+than 256 and up to 512 (G < 8), and the list itself is no shorter, so a small batch with a large task target is planned and
 streamed in one launch and run task by task behind pkv_plan; both must agree bitwise.
 Rectangular grids change kernels at 1536 and 6144 slots, and between 257 and 1535 at slots of
 more than 16 pages."""
@@ -92,6 +92,74 @@ def test_stream_of_large_batches(hq, hkv, B, target):
         two, _, _ = planned(case, 16, p, fused=False)
         assert torch.equal(out, fused) and torch.equal(out, two), step
     assert_close(out, ref_decode(case.q, case.k, case.v, case.bt, case.lens), f"B={B} G={hq // hkv}")
+    assert pkv.pkv_check_device_status(bufs.ws) == 0
+
+
+def own_list(lens, hkv, splits, apart):
+    """A task list in a plan's order with the caller's own ranges: rows where `apart` are cut at other
+    tokens for every second KV head."""
+    tasks, offsets = [], [0]
+    for row, n in enumerate(lens.tolist()):
+        ns = min(splits, -(-n // 16))
+        for s in range(ns):
+            for h in range(hkv):
+                shift = 16 if apart[row] and h % 2 else 0
+                cut = [min(n, (i * n // ns) // 16 * 16 + shift * (0 < i < ns)) if i < ns else n for i in (s, s + 1)]
+                tasks.append((row, h, s, cut[0], cut[1]))
+        offsets.append(offsets[-1] + ns)
+    return np.array(tasks, dtype=np.int32), np.array(offsets, dtype=np.int32)
+
+
+def put_list(bufs, tasks, offsets):
+    bufs.tasks[: len(tasks)] = torch.from_numpy(tasks).cuda()
+    bufs.split_offsets.copy_(torch.from_numpy(offsets))
+    bufs.num_tasks.fill_(len(tasks))
+
+
+@pytest.mark.parametrize("hq,hkv", HEADS)
+@pytest.mark.parametrize("kind", ["plan", "some", "all", "short"])
+def test_lists_of_the_callers_own(hq, hkv, kind):
+    """Behind pkv_plan, lists in a plan's order whose neighbours are not always KV heads g and g + 1 of
+    one range (none, some rows, all), and a list far shorter than the batch lets expect: against the
+    oracle, fused and two-kernel bitwise alike."""
+    rng = np.random.Generator(np.random.PCG64(77))
+    B = 120
+    lens = rng.integers(300, 900, size=B).astype(np.int32)
+    if kind == "short":
+        lens[5:] = 0
+    case = Case(lens, hq=hq, hkv=hkv, seed=77)
+    apart = {"plan": np.zeros(B), "some": rng.random(B) < 0.2, "all": np.ones(B), "short": np.ones(B)}[kind]
+    tasks, offsets = own_list(case.lens, hkv, 4, apart)
+    assert 4 * B * hkv > 768 and (len(tasks) > 768) == (kind != "short")
+    bufs = bufs_for(case, 4)
+    put_list(bufs, tasks, offsets)
+    fused, two = run_decode(case, bufs), run_decode(case, bufs, fused=False)
+    assert torch.equal(fused, two)
+    assert_close(fused, ref_decode(case.q, case.k, case.v, case.bt, case.lens), f"{kind} G={hq // hkv}")
+    assert torch.equal(run_decode(case, bufs), fused)
+    assert pkv.pkv_check_device_status(bufs.ws) == 0
+
+
+@pytest.mark.parametrize("fused", [True, False])
+def test_records_that_are_no_tasks_are_flagged(fused):
+    """Records outside the batch in a list long enough to stream: flagged, the other rows unchanged, and
+    the workspace usable again once the status has been read."""
+    case = Case(np.full(60, 500, dtype=np.int32), seed=78)
+    tasks, offsets = own_list(case.lens, 8, 4, np.zeros(60))
+    assert len(tasks) > 768
+    bufs = bufs_for(case, 4)
+    put_list(bufs, tasks, offsets)
+    clean = run_decode(case, bufs, fused=fused)
+    for at, word, value in [(100, 0, 60), (101, 0, -1), (333, 1, 8), (800, 3, -16), (900, 4, 1 << 20), (901, 4, 0)]:
+        bad = tasks.copy()
+        bad[at, word] = value
+        put_list(bufs, bad, offsets)
+        out = run_decode(case, bufs, fused=fused)
+        assert pkv.pkv_check_device_status(bufs.ws) & pkv.PKV_DEVERR_TASK
+        ok = [r for r in range(60) if r != tasks[at, 0]]
+        assert torch.equal(out[ok], clean[ok]), (at, word)
+    put_list(bufs, tasks, offsets)
+    assert torch.equal(run_decode(case, bufs, fused=fused), clean)
     assert pkv.pkv_check_device_status(bufs.ws) == 0
 
 
