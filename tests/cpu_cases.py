@@ -33,6 +33,9 @@ def compiler():
 def build(folder, csrc=CSRC):
     """The program of the sources in `csrc` (seconds)."""
     flags = [compiler(), "-std=c++17", "-O2", "-fno-pie", "-ffp-contract=off", "-w", "-I", DEVICE, "-I", csrc]
+    with open("/proc/cpuinfo") as f:
+        have = set(re.findall(r"\b(?:fma|f16c)\b", f.read()))
+    flags += [f"-m{x}" for x in sorted(have)]  # else in software: the same values, much slower
     units = [(os.path.join(csrc, "pkv_kernels.hip"), "kernels"), (os.path.join(csrc, "pkv_capi.cpp"), "capi"),
              (os.path.join(DEVICE, "emu.cpp"), "emu"), (os.path.join(DEVICE, "main.cpp"), "main")]
     objs, jobs = [], []

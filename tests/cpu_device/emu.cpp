@@ -158,18 +158,25 @@ void run(const void* kernel_at, dim3 grid, dim3 block, const std::function<void(
       rng = rng * 6364136223846793005ull + 1442695040888963407ull;
       const int pick = order == 0 ? ready.front() : order == 1 ? ready.back() : ready[(rng >> 33) % ready.size()];
       Wave& w = waves[pick];
-      bool any = false;
-      for (int l = 0; l < w.n; ++l) any |= w.lane[l].state == kRunning;
-      if (!any) {  // all arrived at the cross-lane operation
-        ++w.parity;
-        for (int l = 0; l < w.n; ++l)
-          if (w.lane[l].state == kWave) w.lane[l].state = kRunning;
-      }
-      for (int l = 0; l < w.n; ++l)
-        if (w.lane[l].state == kRunning) {
-          cur = &w.lane[l];
-          emu_switch(&scheduler_sp, cur->sp);
+      // On to a barrier, the end, or a sleep; in a pseudo-random schedule also anywhere between.
+      for (bool on = true; on;) {
+        bool any = false;
+        for (int l = 0; l < w.n; ++l) any |= w.lane[l].state == kRunning;
+        if (!any) {  // all arrived at the cross-lane operation
+          ++w.parity;
+          for (int l = 0; l < w.n; ++l)
+            if (w.lane[l].state == kWave) w.lane[l].state = kRunning;
         }
+        bool other = false;
+        for (int l = 0; l < w.n; ++l)
+          if (w.lane[l].state == kRunning) {
+            cur = &w.lane[l];
+            emu_switch(&scheduler_sp, cur->sp);
+            other |= cur->state != kWave;
+          }
+        rng = rng * 6364136223846793005ull + 1442695040888963407ull;
+        on = !other && !w.yielded && (order <= 1 || (rng >> 33) % 8 != 0);
+      }
       cur = nullptr;
     }
   }
