@@ -2680,18 +2680,27 @@ __global__ __launch_bounds__(W * 64) void page_read_kernel(PageReadArgs a) {
   if (hold[(threadIdx.x + 1) % (W * 64)] == 0x9E3779B9u) *a.sink = x;  // keeps the loads; practically never taken
 }
 
+// Compute units of the device (of the first one that asks).
+int compute_units() {
+  static const int n = [] {
+    int dev = 0, cus = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
+      cus = 256;
+    return cus;
+  }();
+  return n;
+}
+
 // Workgroups of `kernel` resident on the current device at once (occupancy x CUs),
 // at least one per CU. The split kernels loop over tasks with the grid as stride, so
 // their grid is the task bound capped at this count (taken once per kernel, on the
 // first device that launches it).
 int resident_blocks(const void* kernel, int threads) {
-  int dev = 0, cus = 0, per_cu = 0;
-  if (hipGetDevice(&dev) != hipSuccess ||
-      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
-    cus = 256;
+  int per_cu = 0;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, threads, 0) != hipSuccess || per_cu < 1)
     per_cu = 1;
-  return per_cu * cus;
+  return per_cu * compute_units();
 }
 
 // Kernels go out through hipExtLaunchKernelGGL: with events it stamps `start` when the
@@ -2729,6 +2738,7 @@ hipError_t launch_decode_g(const DecodeArgs& a, int mode, int grid, hipStream_t 
     const int64_t tiles = ((int64_t)a.max_pages * P + a.tile_tokens - 1) / a.tile_tokens;
     const int64_t slot_pages = (tiles + a.S - 1) / a.S * (a.tile_tokens / P);
     const bool even = a.Hkv % 2 == 0;
+    const int cus = compute_units();  // (256 in the figures below)
     bool pairs, dense;  // two heads per workgroup; the dense kernel
     if constexpr (on_matrix_cores<G>()) {
       // A slot of at most two pages per wave is a chain of round trips more than a read. Beyond one
@@ -2742,23 +2752,23 @@ hipError_t launch_decode_g(const DecodeArgs& a, int mode, int grid, hipStream_t 
       // 8250 tokens, 1664 slots: 46 against 48 us; 21 rows of up to 39 K, 1344 slots: 146 against
       // 139), and from twelve rounds of them on two slots per workgroup beat one (60 rows of up
       // to 4096 tokens, 7680 slots: 103 against 112 us; 2560 slots: 86 against 82).
-      dense = slots >= 6 * 256;
-      pairs = even && (dense ? slots >= 12 * 512 : G <= 4 && slots > 256 && slot_pages <= 2 * W);
+      dense = slots >= 6 * cus;
+      pairs = even && (dense ? slots >= 24 * cus : G <= 4 && slots > cus && slot_pages <= 2 * W);
     } else if (G == 1) {
       // Without staged pages two one-head workgroups fit a compute unit. Pairs pay as soon as one
       // round of those does not hold the slots (Hkv = 32, 1024 slots of rows of 1500 tokens 11.4 ->
       // 9.9 us, 32 rows 122.6 -> 93.7; 512 slots of 24 K tokens 17.0 against 21.4). An odd head
       // left over: short slots dense from six per compute unit on (Hkv = 3, 64 rows of 1500
       // tokens 28.6 -> 24.8 us, 24 K tokens 115 against 122).
-      pairs = even && slots > 2 * 256;
-      dense = !even && slots >= 6 * 256 && slot_pages <= 2 * W;
+      pairs = even && slots > 2 * cus;
+      dense = !even && slots >= 6 * cus && slot_pages <= 2 * W;
     } else {
       // G = 2: one by one, dense (three workgroups a unit) from six slots per compute unit on
       // (Hkv = 16: 2048 slots of rows of 1500 tokens 23.8 -> 22.4 us, 16384 of 400 tokens 83 -> 78;
       // pairs of heads in the dense kernel 83 and 141 against 79 and 138, rows of 64 tokens 52
       // against 44), with an odd head short slots only (Hkv = 3, 32 rows of 24 K tokens 124 against 118).
       pairs = false;
-      dense = slots >= 6 * 256 && (even || slot_pages <= 2 * W);
+      dense = slots >= 6 * cus && (even || slot_pages <= 2 * W);
     }
     hipError_t e;
     if (dense && pairs) e = launch(rect_dense_kernel<G, W, on_matrix_cores<G>() ? 2 : 1>, slots / 2, W * 64, s, start, nullptr, a);

@@ -222,3 +222,24 @@ def test_records_that_are_no_tasks_are_flagged(program, route, compute_units):
     (a,), _ = c.run(program, route, params(2), given=(tasks, wrong), compute_units=compute_units)
     assert a.error_bits & TASK
     close(a.out[:5], ref[:5])
+
+
+@pytest.mark.parametrize("hq,hkv", HEADS + [(3, 3), (12, 3)])
+@pytest.mark.parametrize("S,longest", [(2, 600), (4, 300), (9, 300)])
+def test_rectangular_kernels(program, hq, hkv, S, longest):
+    """Pairs of heads, the dense kernel and both together are chosen by slots per compute unit of the
+    device, and give the bits of one slot per workgroup; empty splits and rows, named rows."""
+    lens = [longest, 1, 0, 33, 17, 200]
+    c = Call(lens, hq=hq, hkv=hkv, seed=11)
+    seen = set()
+    base = None
+    for compute_units in (256, 16, 8, 3, 1):
+        (a,), launched = c.run(program, "rect", params(hkv), S=S, order=DESCENDING, compute_units=compute_units)
+        seen.add(kernels(launched)[0].split("<")[0] + kernels(launched)[0][-3:])
+        base = a.out if base is None else base
+        assert a.status == 0 and a.error_bits == 0
+        assert np.array_equal(a.out.view(np.uint16), base.view(np.uint16)), (compute_units, launched)
+        (b,), _ = c.run(program, "rect", params(hkv), S=S, row_ids=[5, 0, 2], compute_units=compute_units)
+        assert np.array_equal(b.out[[5, 0, 2]].view(np.uint16), base[[5, 0, 2]].view(np.uint16))
+    close(base, reference(c))
+    assert len(seen) >= 2 or (hkv % 2 and hq // hkv <= 2 and longest > 256 * S), seen  # long slots, odd head: one by one
