@@ -22,9 +22,13 @@ value = decode tokens / second = sum of active rows over the timed steps / sum o
 times (event intervals around the step, marker latency included). roofline.achieved =
 algorithmic bytes of one decode-kernel launch / its average execution time (start and
 stop events stamped by the launch itself, hipExtLaunchKernel, so the interval is the
-kernel's own, as rocprofv3 reports it). extra.beta_read_gbs is the streaming-read
+kernel's own, as rocprofv3 reports it). extra.calibration holds the streaming-read
 bandwidth of the 1 GiB eviction read in the same run (the calibration probe beta).
 cpu_baseline = the fp64 numpy oracle on the host over the same steps' inputs.
+
+The printed line holds what each workload measured in a few figures, so that it stays a
+few kilobytes; --details PATH writes everything (per-seed results, every route's table,
+the cost model's estimates) to a file.
 """
 from __future__ import annotations
 
@@ -499,6 +503,32 @@ CAL_RUNS = ([(w, "one-launch", 1, t) for w in ("b1", "b8_bimodal") for t in (128
                for r in ("plan+fused", "two-kernel", "rect", "coarse-buckets")])
 
 
+def short(x, digits=6):
+    """`x` with its floats rounded to `digits` significant digits."""
+    if isinstance(x, dict):
+        return {k: short(v, digits) for k, v in x.items()}
+    if isinstance(x, (list, tuple)):
+        return [short(v, digits) for v in x]
+    return float(f"{x:.{digits}g}") if isinstance(x, float) else x
+
+
+def short_extra(extra, workloads):
+    """The printed line's extra: per workload its rate, step and kernel time, bandwidth and how it was
+    cut; of the seeds, mean and std; of the route tables, the step times."""
+    keys = ("tok_s", "ms_per_step", "decode_ms", "decode_gbs", "page_read_gbs", "task_target", "kv_heads_per_workgroup")
+    out = {w: {k: extra[w][k] for k in keys if k in extra[w]} for w in workloads}
+    out["calibration"] = extra["calibration"]
+    if "seeds" in extra:
+        out["seeds"] = {w: {k: v[k] for k in ("tok_s_mean", "tok_s_std")} for w, v in extra["seeds"].items()}
+    for k, table in extra.items():
+        if k.startswith("routes_"):
+            out[k] = {route: v["ms_per_step"] for route, v in table.items()}
+    model = extra.get("cost_model")
+    if model:
+        out["cost_model"] = {k: model[k] for k in ("chosen", "measured_fastest") if k in model}
+    return out
+
+
 def dataclass_dict(x):
     import dataclasses
     return dataclasses.asdict(x)
@@ -601,6 +631,7 @@ def main():
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--hkv", type=int, default=8, choices=(4, 8, 16, 32),
                     help="KV heads (Hq = 32, so G = 32 / hkv: 8 -> G=4, 32 -> G=1, 4 -> G=8)")
+    ap.add_argument("--details", metavar="PATH", help="also write the full result, with every table, to PATH")
     ap.add_argument("--calibrate", metavar="PATH",
                     help="fit the route cost model (C_min, T_0) on the CAL_RUNS steps, write it to PATH, print "
                          "measured against modelled step times as one JSON line, and exit")
@@ -721,7 +752,10 @@ def main():
             **{f"{k}_step_tok_s": val for k, val in oracle_also.items()}},
         "extra": extra,
     }
-    print(json.dumps(line))
+    if args.details:
+        with open(args.details, "w") as f:
+            json.dump(line, f)
+    print(json.dumps(short({**line, "extra": short_extra(extra, [args.workload] + also)})))
 
 
 if __name__ == "__main__":

@@ -56,6 +56,26 @@ def test_head_pair_report():
     assert not bench.head_pairs(32, 4, 512) and not bench.head_pairs(32, 32, 1024)
 
 
+def test_the_printed_line_stays_short():
+    """What keeps the end of a run's output keeps the whole line: every table at full length is some
+    30 kB, the printed part a few."""
+    import json
+
+    x = 1234.567890123456
+    one = {k: x for k in ("tok_s", "ms_per_step", "decode_ms", "decode_gbs", "wall_tok_s", "step_gbs", "plan_ms",
+                          "page_read_gbs", "alg_bytes_per_launch", "kv_bytes_per_step")}
+    one.update(task_target=512, kv_heads_per_workgroup=2, cost_model={"estimate_us": {r: x for r in bench.ROUTES}})
+    names = ["b1", "b8_bimodal", "b8_uniform", "b8_zipf", "b4_bimodal"]
+    seeds = {w: {"per_seed": {str(s): dict(one) for s in range(5)}, "tok_s_mean": x, "tok_s_std": x} for w in names}
+    extra = {**{w: dict(one) for w in names}, "calibration": {"beta_read_gbs": x, "launch_gap_us": x}, "seeds": seeds,
+             **{"routes_" + w: {r: dict(one) for r in bench.ROUTES} for w in names[:3]},
+             "cost_model": {"chosen": "one-launch", "measured_fastest": "one-launch", "estimate_us": {}}}
+    got = bench.short(bench.short_extra(extra, names))
+    assert len(json.dumps(got)) < 3000
+    assert got["b8_zipf"]["tok_s"] == 1234.57 and got["b1"]["task_target"] == 512
+    assert got["routes_b1"]["rect"] == 1234.57 and got["seeds"]["b1"] == {"tok_s_mean": 1234.57, "tok_s_std": 1234.57}
+
+
 def test_more_than_one_gpu_is_refused():
     r = subprocess.run([sys.executable, os.path.join(ROOT, "bench.py"), "--gpus", "2"], capture_output=True,
                        text=True, timeout=120)
