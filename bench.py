@@ -332,13 +332,11 @@ def head_pairs(hq, hkv, target):
 
 
 def heads_per_workgroup(runner):
-    """KV heads that a workgroup of the measured decode kernel reads together: pairs on the
-    one-launch route at G <= 4 from two tasks per resident workgroup on."""
+    """KV heads that a workgroup of the measured decode kernel reads together."""
     from paper_2606_26666_amd import costmodel
     w = runner.w
-    pairs = head_pairs(w.hq, w.hkv, w.target_tasks) or (
-        w.hq // w.hkv <= 2 and w.hkv % 2 == 0 and w.target_tasks >= 2 * costmodel.CUS)
-    return 2 if runner.route == "one-launch" and pairs else 1
+    tasks = int(runner.bufs.num_tasks.item()) if runner.route in costmodel.LAUNCHES else 0
+    return costmodel.heads_per_workgroup(runner.route, w.hq, w.hkv, w.batch, w.target_tasks, tasks)
 
 
 def split_range(runner, lens):

@@ -81,7 +81,7 @@ class RouteShape:
     merge_bytes: int
     merge_launches: int
     route: str = "one-launch"
-    pairs: bool = False       # the one-launch route runs KV-head pairs
+    pairs: bool = False       # the task target was raised for KV-head pairs (one-launch, G = 4)
 
     @property
     def workgroups(self) -> int:
@@ -100,6 +100,28 @@ def head_pairs(hq: int, hkv: int) -> bool:
     does so, at G <= 4, when the task target is at least two tasks per resident
     workgroup; at G = 1 and 2 the target is that high by the KV heads alone."""
     return hkv > 0 and hq % hkv == 0 and hq // hkv == 4 and hkv % 2 == 0
+
+
+def stream_pays(G: int, tasks: int, paired: bool, cus: int = CUS) -> bool:
+    """The library's rule for running tasks as a stream of KV-head pairs, one workgroup per compute
+    unit: from eight tasks per workgroup where head pairs are the alternative, else from four rounds of
+    tasks on, or at two (G < 8)."""
+    if paired:
+        return tasks >= 8 * cus
+    return tasks > 3 * cus or (G < 8 and cus < tasks <= 2 * cus)
+
+
+def heads_per_workgroup(route: str, hq: int, hkv: int, batch: int, target: int, tasks: int) -> int:
+    """KV heads that a workgroup of a workqueue route's decode kernel reads together: two where the
+    library runs KV-head pairs or a stream of them, else one. The one-launch route decides by the task
+    target; behind pkv_plan, four tasks per row and KV head are expected, and the list's own length
+    (`tasks`) is looked at on the device."""
+    G = hq // hkv
+    if hkv % 2 or route not in LAUNCHES:
+        return 1
+    if route == "one-launch":
+        return 2 if stream_pays(G, target, G < 8) or (G <= 4 and target >= 2 * CUS) else 1
+    return 2 if stream_pays(G, 4 * batch * hkv, False) and stream_pays(G, tasks, False) else 1
 
 
 PAIR_MAX_SPLITS = 24  # splits per (row, KV head) up to which KV-head pairs pay

@@ -6,6 +6,7 @@ import numpy as np
 import pytest
 
 from oracle import ref_decode
+from paper_2606_26666_amd import costmodel
 from tests import cpu_cases
 from tests.cpu_cases import ASCENDING, DESCENDING, Call
 
@@ -243,3 +244,21 @@ def test_rectangular_kernels(program, hq, hkv, S, longest):
         assert np.array_equal(b.out[[5, 0, 2]].view(np.uint16), base[[5, 0, 2]].view(np.uint16))
     close(base, reference(c))
     assert len(seen) >= 2 or (hkv % 2 and hq // hkv <= 2 and longest > 256 * S), seen  # long slots, odd head: one by one
+
+
+@pytest.mark.parametrize("route,name", [("plan_decode", "one-launch"), ("fused", "plan+fused"), ("separate", "two-kernel")])
+@pytest.mark.parametrize("hq,hkv,B", [(2, 2, 9), (4, 4, 17), (8, 2, 33), (32, 4, 20), (32, 4, 49), (3, 3, 70), (16, 2, 97)])
+def test_reported_heads_per_workgroup(program, route, name, hq, hkv, B):
+    """What the benchmark reports of a launch on 256 compute units, against the kernel that is launched
+    there (pairs and streams read two heads)."""
+    c = Call([1] * B, hq=hq, hkv=hkv, seed=12)
+    for target in (256, 511, 512, 768, 769, 2047, 2048):
+        _, launched = c.run(program, route, params(hkv, split_max=1, target=target, policy=0), compute_units=256)
+        kernel = [k for k in kernels(launched) if k.startswith(("split_kernel", "stream_kernel"))][0]
+        two = kernel.startswith("stream") or kernel.endswith(" 2>")
+        tasks = 10 ** 6  # the launch: the host's part of the rule
+        assert costmodel.heads_per_workgroup(name, hq, hkv, B, target, tasks) == 1 + two, (target, kernel)
+        if name != "one-launch":
+            break
+    assert costmodel.heads_per_workgroup("rect", hq, hkv, B, 4096, 0) == 1
+    assert costmodel.heads_per_workgroup("plan+fused", 32, 8, 64, 2048, 256) == 1  # a short list runs task by task
