@@ -164,7 +164,10 @@ int pkv_plan_host(const int32_t* seq_lens, int32_t B, int32_t max_pages_per_row,
  *              last split of each (row, KV head) to finish merges, in split order
  *   out        device fp16 [B, Hq, d]; rows with seq_len 0 are written as zeros
  *   ws         workspace of at least pkv_workspace_size(B, Hq, Hkv, d, max_tasks) bytes
- * Both flag values give bit-identical outputs. Supported: d = 128, G in {1,2,4,8}. */
+ * Both flag values give bit-identical outputs. Supported: d = 128, G in {1,2,4,8}.
+ * With G <= 2 the softmax weights are fp32 throughout; with G >= 4 they are multiplied with
+ * V as two fp16 halves (22 bits down to 2^-17 of the row's largest weight, an error of 2^-39
+ * of it below), and a V that is infinite can then give NaN instead of infinity. */
 int pkv_decode(const uint16_t* q, const uint16_t* k_cache, const uint16_t* v_cache,
                int32_t num_pages, const int32_t* block_table, int32_t max_pages_per_row,
                const int32_t* seq_lens, int32_t B, int32_t Hq, int32_t Hkv, int32_t d,
@@ -174,8 +177,8 @@ int pkv_decode(const uint16_t* q, const uint16_t* k_cache, const uint16_t* v_cac
 
 /* pkv_plan followed by pkv_decode with PKV_FUSED_MERGE, in one kernel launch: every
  * workgroup runs the planner's arithmetic on seq_lens and takes its task from the
- * result, and the first workgroup also writes tasks, split_offsets and num_tasks exactly
- * as pkv_plan writes them. Arguments as for pkv_plan and pkv_decode; the block table is
+ * result, and the launch also writes tasks, split_offsets and num_tasks exactly as
+ * pkv_plan writes them. Arguments as for pkv_plan and pkv_decode; the block table is
  * checked by the decode (not by the planner), B <= 1024, params->num_kv_heads == Hkv.
  * The completion counters must be zero at launch: pkv_workspace_init zeroes them,
  * and every completed pkv_plan, pkv_plan_decode or pkv_decode call leaves them zero,
@@ -183,15 +186,17 @@ int pkv_decode(const uint16_t* q, const uint16_t* k_cache, const uint16_t* v_cac
  * (PKV_DEVERR_TASK): such a call may leave counters short of their split count, and
  * pkv_check_device_status re-zeroes them when it reports the error (for a workspace
  * set up by pkv_workspace_init; pkv_plan also zeroes them).
- * The previous contents of `tasks` (for B <= 64) are read as a scheduling hint: each
- * workgroup starts loading the task listed at its own index while the planner runs and
- * keeps those loads only if the new plan gives it the same pages. Any contents are
- * allowed (out-of-range records are ignored) and never change a result.
+ * The previous contents of `tasks` (for B <= 64, and with many tasks per workgroup for
+ * every B) are read as a scheduling hint: each workgroup starts loading the task listed at
+ * its own index while the planner runs and keeps those loads only if the new plan gives it
+ * the same pages. Any contents are allowed (out-of-range records are ignored) and never
+ * change a result.
  * With G <= 4, Hkv even and params->target_tasks at least twice the workgroups the
  * device holds at once (512 on MI355X), each workgroup runs two tasks together: KV heads
  * g and g + 1 of one split, whose slices of each token are adjacent (its hint is then
- * the record at twice its index); with many tasks per workgroup (Hkv even) it runs all its
- * pairs as one stream of pages. This changes only which workgroup computes what.
+ * the record at twice its index); with many tasks per workgroup (Hkv even; a target of
+ * 2048 on MI355X, 769 at G = 8) it runs all its pairs as one stream of pages. This changes
+ * only which workgroup computes what.
  * Outputs are bit-identical to the two-call sequence. */
 int pkv_plan_decode(const uint16_t* q, const uint16_t* k_cache, const uint16_t* v_cache,
                     int32_t num_pages, const int32_t* block_table, int32_t max_pages_per_row,
@@ -313,7 +318,8 @@ int pkv_stream_read_nt_timed(const void* src, size_t bytes, uint32_t* sink, hipS
  * contiguous stream). For each of the first min(*num_tasks, max_tasks) records of
  * `tasks` (as pkv_plan / pkv_plan_decode write them), the K and V bytes of the task's
  * KV heads over the pages of its token range are read with the loads, waves, loads in
- * flight, grid and task-to-workgroup mapping of the one-launch decode kernel:
+ * flight, grid and (up to three rounds of tasks per workgroup) task-to-workgroup mapping
+ * of the one-launch decode kernel:
  * heads_per_workgroup = 1 runs one task per workgroup, 2 the tasks 2p and 2p + 1 (KV
  * heads g, g + 1) together, as the decode's KV-head pairs do. No query is read, nothing
  * is computed or written except `sink`, a device word written only if the data hash to

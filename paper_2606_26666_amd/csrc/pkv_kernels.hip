@@ -155,9 +155,10 @@ __device__ __forceinline__ void st_state4(__amdgpu_buffer_rsrc_t r, int off, v4f
 // Merge of split states (Sec. 3.3): M = max m_s, L = sum 2^(m_s-M) l_s,
 // A = sum 2^(m_s-M) a_s, O = A / L. The sums follow one fixed tree: runs of kMergeRun
 // consecutive splits, each summed in split order from zero, and the run sums added in
-// order, so the result depends neither on the thread count nor on the route. Every
-// merge in the library goes through merge_group, so all routes round identically. A
-// (row, KV head) with a marked split (l < 0) is zeroed.
+// order, so the result depends neither on the thread count nor on the route. merge_group
+// does this for a workgroup; merge_columns (several merges side by side, in the stream) and
+// finish_task's direct output (one split) go through the same operations in the same order,
+// which the tests compare bit by bit. A (row, KV head) with a marked split (l < 0) is zeroed.
 //
 // Up to 64 splits (eight runs) the column path below reads only existing states. Beyond
 // that, the general path: a first pass over blocks of kMergeBlock states for the
@@ -488,9 +489,9 @@ __device__ __forceinline__ void merge_group(__amdgpu_buffer_rsrc_t pr, int slot0
 
 // The column path for a team of GH * D / 4 threads (one KV head; thread c of the team owns
 // output elements 4c .. 4c + 3) that merges nsplit <= 64 states by itself: the runs one after
-// another, so a workgroup can merge several (row, KV head)s side by side, one per team. `ns_max`: the largest nsplit among the
-// wave's teams (G = 1 has two in a wave). wl: 128 (weight, l) pairs of LDS per wave. The
-// operations and their order are merge_group's.
+// another, so a workgroup can merge several (row, KV head)s side by side, one per team.
+// `ns_max`: the largest nsplit among the wave's teams (G = 1 has two in a wave). wl: 128
+// (weight, l) pairs of LDS per wave. The operations and their order are merge_group's.
 template <int G, bool COHERENT>
 __device__ __forceinline__ void merge_columns(__amdgpu_buffer_rsrc_t pr, int slot0, int stride, int nsplit, int ns_max,
                                               int c, uint16_t* __restrict__ out_grp, v2f* wl) {
@@ -562,8 +563,9 @@ __device__ __forceinline__ void merge_columns(__amdgpu_buffer_rsrc_t pr, int slo
 // in LDS, each combined exactly as a one-head task's.
 // Layout of the wave states in LDS: (m, l) pairs [NH][W][G] (l = -1: the wave met an invalid
 // page), then acc [NH][W][G][kHeadPitch]. The pitch of a head's D columns puts the matrix
-// bodies' stores of several heads at once on distinct banks (at D floats the heads of one
-// store share their banks: 0.9 instead of 0.3 us per state of two KV heads).
+// body's stores of several heads at once on distinct banks (at D floats the heads of one store
+// share their banks: 256 short rows at G = 8 169.5 instead of 154.3 us, 256 one-tile rows 33.5
+// instead of 28.8, long tasks alike).
 // `direct`: the task is its row's only split, so its state is the merged state: the output
 // goes there at once (the arithmetic of a one-split merge: weight 1, sums started at +0) and
 // no state is stored. Threads tid, tid + NT, ... take the columns. `heads`: how many of the NH.
@@ -1556,11 +1558,11 @@ __device__ __forceinline__ TaskRec plan_task(const PlanArgs& a, const PlanLds& L
 }
 
 // Units `from` .. count (per_split units a split: tasks, or pairs of them) cut into `parts`
-// contiguous ranges of about the same weight: the first unit of range w. A row's weight, its tiles plus one per split, is spread evenly over
-// its units, and a bound is a whole number of units, so that
-// neighbours agree on their common bound.
-__device__ __forceinline__ int plan_range_begin(const PlanArgs& a, const PlanLds& L, int per_split, int w, int parts, int from,
-                                                int count) {
+// contiguous ranges of about the same weight: the first unit of range w. A row's weight, its
+// tiles plus one per split, is spread evenly over its units, and a bound is a whole number of
+// units, so that neighbours agree on their common bound.
+__device__ __forceinline__ int plan_range_begin(const PlanArgs& a, const PlanLds& L, int per_split, int w, int parts,
+                                                int from, int count) {
   if (w <= 0) return from;
   if (w >= parts) return count;
   auto row_of = [&](const int* v, int x) {  // largest i with v[i] <= x
@@ -1871,7 +1873,8 @@ __global__ __launch_bounds__(W * 64) void split_kernel(DecodeArgs a) {
 // of tasks, KV heads g and g + 1 of one split (adjacent 256-byte slices of every token, which
 // read faster than one head's). A wave keeps one page of each head in flight: it waits for
 // one, stages it in LDS, at once issues the loads of its next page of that head, and computes
-// from LDS. The page after a unit's last is the next unit's first, so the reads go on while a
+// from LDS (on the vector ALU the next K is issued after the scores, the next V after the
+// sums). The page after a unit's last is the next unit's first, so the reads go on while a
 // unit is combined, stored, counted and merged, and what a unit leaves behind rides on the
 // waits of the ones after it: its state stores have been acknowledged when the second next
 // unit's first page is there, its completion counter is bumped in that unit's epilogue, and
@@ -1879,6 +1882,7 @@ __global__ __launch_bounds__(W * 64) void split_kernel(DecodeArgs a) {
 // Every task goes through exactly the operations of the one-task kernels in their order
 // (eight waves taking its pages round-robin, the same combine and merge), so results are
 // bitwise the same.
+//
 // Whether `tasks` tasks run as a stream of KV-head pairs, `slots` (one per compute unit)
 // at a time, rather than on the one-task kernels. The stream goes through ceil(tasks / 2 slots)
 // rounds of units of two tasks each, the one-task kernels through ceil(tasks / slots) rounds
@@ -2043,8 +2047,8 @@ __global__ __launch_bounds__(W * 64) void stream_kernel(DecodeArgs a) {
   // The host chose this kernel by the tasks it expects of the batch. Where the list is shorter
   // (empty or short rows) and its tasks are better run one by one, they are: the stream's units
   // would leave half of the compute units without work (64 rows, 58 of them empty, one plan and
-  // two layers: G = 8 77 -> 54 us, G = 1 70 -> 52).
-  // Ahead of all else, or the stream would carry what both need in registers of its own.
+  // two layers: G = 8 77 -> 54 us, G = 1 70 -> 52). Ahead of all else: after the stream's set-up
+  // it shares that one's values and costs every launch 0.5 us.
   int ntasks = 0;
   const int grid = gridDim.x;
   if (!PLAN) {
@@ -2612,7 +2616,8 @@ __global__ __launch_bounds__(256) void read_kernel(const v4u* __restrict__ src, 
 // 16-byte buffer loads of K and four of V, each covering four whole 256-byte rows; two
 // (page, head) units in flight per wave: two pages of one head, or one page of each of
 // two heads), with the decode's grid (one workgroup per compute unit, held by the LDS
-// reservation) and task-to-workgroup mapping. Nothing else: no queries, no arithmetic
+// reservation) and, as long as tasks are dealt in strides (the one-task kernels, and streams
+// of up to three rounds), its task-to-workgroup mapping. Nothing else: no queries, no arithmetic
 // beyond folding the bytes into a sink word, no state, no merge. Its time is the read
 // time of the decode's pages in the decode's pattern.
 constexpr int kPageReadHoldWords = 24 * 1024;  // 96 KiB of LDS: one workgroup per compute unit
