@@ -64,8 +64,9 @@ struct DecodeArgs {
   int32_t max_pages_per_row;
   int32_t B, Hq, Hkv;
   int32_t max_tasks;
-  int32_t slots;        // stream behind pkv_plan: workgroups the device holds at once
-  int32_t S;            // rectangular route only
+  int32_t S;            // rectangular route: slots per row and KV head; stream behind pkv_plan: the
+                        // workgroups the device holds at once (no field of its own: the planner's
+                        // part below would then cross a scalar-cache line, 0.2 us a launch)
   int32_t tile_tokens;  // rectangular route only
   int32_t n_rows;       // rectangular route: rows named in row_ids (0: rows 0..B-1)
   float scale_log2;     // sm_scale * log2(e)

@@ -2055,7 +2055,7 @@ __global__ __launch_bounds__(W * 64) void stream_kernel(DecodeArgs a) {
     ntasks = uniform(*a.num_tasks);
     if (ntasks > a.max_tasks) ntasks = a.max_tasks;
   }
-  if (!PLAN && __builtin_expect(!stream_pays(G, ntasks, a.slots, false), 0)) {
+  if (!PLAN && __builtin_expect(!stream_pays(G, ntasks, a.S, false), 0)) {
     for (int t = blockIdx.x; t < ntasks; t += grid) {
       const int* tp = reinterpret_cast<const int*>(a.tasks + t);
       lone_task<G, W, FUSED>(a, t, TaskRec{uniform(tp[0]), uniform(tp[1]), uniform(tp[2]), uniform(tp[3]), uniform(tp[4])},
@@ -2730,7 +2730,7 @@ int stream_slots() {
 }
 
 DecodeArgs with_slots(DecodeArgs a, int slots) {
-  a.slots = slots;
+  a.S = slots;
   return a;
 }
 
