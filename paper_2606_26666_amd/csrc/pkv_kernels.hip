@@ -636,8 +636,9 @@ __device__ __forceinline__ void finish_task(const DecodeArgs& a, int slot, float
 
 // ---------------------------------------------------------------------------------
 // The task body on the matrix cores (G = 4 and 8): the path is 4 flop per byte at G = 4, far
-// below their rate, but the vector form spends its issue slots on dot products and FMAs (G = 4,
-// 32 K tokens: 32.3 against 28.0 us).
+// below their rate, but the vector form spends its issue slots on dot products and FMAs (G = 4 on
+// the vector ALU: 32 K tokens 28.0 against 25.5 us, 64 chat rows 110 against 94, buckets 117
+// against 100).
 //
 // Per 16-token page of the task's KV head, one wave computes
 //   S[16 tokens x 16] = K_page[16 x 128] . Q^T[128 x 16]       (4 x mfma 16x16x32 f16)
@@ -680,7 +681,8 @@ __device__ __forceinline__ v4u* kv_stage() {
 // compiler keeps their parts, adds them up again on every page and spills some).
 typedef __attribute__((address_space(3))) v4u lds_v4u;
 
-__device__ __forceinline__ int opaque(int x) {
+template <typename T>
+__device__ __forceinline__ T opaque(T x) {
   asm volatile("" : "+v"(x));
   return x;
 }
@@ -924,7 +926,9 @@ struct VectorState {
     for (int h = 0; h < G; ++h) {
       auto meet = [&](auto swap, auto& from, auto& to) __attribute__((always_inline)) {
         constexpr int n = sizeof(to) / sizeof(float);
-        float m0 = m[h], m1 = m[h], l0 = l[h], l1 = l[h];
+        // (the second copies opaque: two results of a swap of one value with itself have been
+        // seen folded into one)
+        float m0 = m[h], m1 = opaque(m0), l0 = l[h], l1 = opaque(l0);
         swap(m0, m1);
         swap(l0, l1);
         const float M = fmaxf(m0, m1);
