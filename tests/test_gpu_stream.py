@@ -234,9 +234,10 @@ def test_short_rectangular_slots_in_pairs(hq, hkv, B, S, extra):
 @pytest.mark.parametrize("target", [256, 2048])
 def test_many_small_weights_add_up(hq, hkv, target):
     """One token holds the maximum and 40000 others have 2^-26 of its weight each, all with
-    V = 1 where the first has 0: the output is their share, 6.0e-4. fp16 weights end at 2^-24,
-    so they are only seen if the product's weights are scaled. Bound: the output's own fp16
-    rounding (2^-11) and 2^-13 (22-bit weights, 13 of whose bits lie above fp16's end)."""
+    V = 1 where the first has 0: the output is their share, 6.0e-4. At G = 4 and 8 weights enter
+    the product in fp16, which ends at 2^-24, so they are only seen if they are scaled. Bound: the
+    output's own fp16 rounding (2^-11) and 2^-13 (a weight's error is 2^-39 of the largest one,
+    2^-13 of itself); at G = 1 and 2, fp32 weights, the first alone would do."""
     n = 40001
     case = Case([n], hq=hq, hkv=hkv, seed=75)
     k = torch.zeros_like(case.k_dev)
